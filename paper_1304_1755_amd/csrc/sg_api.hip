@@ -86,7 +86,7 @@ int ensure_mg(sg_ctx* c, int is_float) {
     const int P = c->hs.P;
     for (size_t l = 0; l < c->levels.size(); ++l) {
         Level& lv = c->levels[l];
-        const size_t cap = (size_t)lv.N * P;
+        const size_t cap = panel_elems(lv.N, P);
         int rc = SG_OK;
         if (is_float && !lv.r32) {
             rc = dalloc(c, &lv.r32, cap);
@@ -932,51 +932,17 @@ int sg_setup(const sg_options* opt, const double* a0_nodal, const double* kl_amp
         lv.nx = lv.n - 1;
         lv.N = lv.nx * lv.nx;
         if ((rc = upload(c, &lv.sten64, hs.mg_sten[l]))) return fail(rc);
-        std::vector<float> s32(hs.mg_sten[l].begin(), hs.mg_sten[l].end());
-        if ((rc = upload(c, &lv.sten32, s32))) return fail(rc);
-        std::vector<double> rd64((size_t)lv.N);
-        std::vector<float> rd32((size_t)lv.N);
-        for (int i = 0; i < lv.N; ++i) {
-            rd64[i] = 1.0 / hs.mg_sten[l][(size_t)i * 9 + 4];
-            rd32[i] = 1.0f / s32[(size_t)i * 9 + 4];
-        }
-        if ((rc = upload(c, &lv.rdiag64, rd64))) return fail(rc);
-        if ((rc = upload(c, &lv.rdiag32, rd32))) return fail(rc);
-        {
-            std::vector<double> p64((size_t)lv.N * 10, 0.0);
-            std::vector<float> p32((size_t)lv.N * 12, 0.0f);
-            for (size_t node = 0; node < (size_t)lv.N; ++node) {
-                for (int e = 0; e < 9; ++e) {
-                    p64[node * 10 + e] = hs.mg_sten[l][node * 9 + e];
-                    p32[node * 12 + e] = s32[node * 9 + e];
-                }
-                p64[node * 10 + 9] = rd64[node];
-                p32[node * 12 + 9] = rd32[node];
-            }
-            if ((rc = upload(c, &lv.stp64, p64))) return fail(rc);
-            if ((rc = upload(c, &lv.stp32, p32))) return fail(rc);
-        }
-        if (lv.nx <= kLdsCycleMaxNx) {
-            // colour q = (x odd when q is even) + (y odd when q < 2), the order of a forward sweep
-            std::vector<double> c64;
-            std::vector<float> c32;
-            for (int q = 0; q < 4; ++q) {
-                const int px = (q & 1) ^ 1, py = (q >> 1) ^ 1;
-                for (int y = py; y < lv.nx; y += 2)
-                    for (int x = px; x < lv.nx; x += 2) {
-                        const size_t node = (size_t)y * lv.nx + x;
-                        for (int e = 0; e < 9; ++e) {
-                            c64.push_back(hs.mg_sten[l][node * 9 + e]);
-                            c32.push_back(s32[node * 9 + e]);
-                        }
-                        c64.push_back(rd64[node]);
-                        c32.push_back(rd32[node]);
-                        c32.push_back(0.0f);
-                        c32.push_back(0.0f);
-                    }
-            }
-            if ((rc = upload(c, &lv.cst64, c64))) return fail(rc);
-            if ((rc = upload(c, &lv.cst32, c32))) return fail(rc);
+        const size_t nn = (size_t)lv.N;
+        if ((rc = dalloc(c, &lv.sten32, nn * 9)) || (rc = dalloc(c, &lv.rdiag64, nn)) || (rc = dalloc(c, &lv.rdiag32, nn)) ||
+            (rc = dalloc(c, &lv.stp64, nn * 10)) || (rc = dalloc(c, &lv.stp32, nn * 12)))
+            return fail(rc);
+        const size_t pairs = (size_t)(lv.nx + 1) * 10 * (lv.nx + 3);
+        if ((lv.nx & 1) && ((rc = dalloc(c, &lv.sps64, pairs)) || (rc = dalloc(c, &lv.sps32, pairs)))) return fail(rc);
+        if (lv.nx <= kLdsCycleMaxNx && ((rc = dalloc(c, &lv.cst64, nn * 10)) || (rc = dalloc(c, &lv.cst32, nn * 12))))
+            return fail(rc);
+        if ((rc = launch_level_setup(c->stream, lv))) {
+            set_error("sg_setup: level setup launch failed");
+            return fail(rc);
         }
     }
     if ((rc = upload_plan(c, make_plan(hs, 0, P, 0, P, true, true, true), c->plan_full))) return fail(rc);

@@ -154,6 +154,11 @@ struct Level {
     // (16-byte pieces) for the narrow row smoother
     double* stp64;
     float* stp32;
+    // the stencils by column pairs for the streaming cycle legs: (nx + 1) rows (the last zeros) of
+    // 10 coefficients x (nx + 3) / 2 pairs (the last zeros; nx odd), the even and the odd column of a
+    // pair adjacent; in float two coefficients of a pair share a 16-byte piece
+    double* sps64;
+    float* sps32;
     // work buffers, capacity N x P
     double* u64; double* f64; double* r64; double* w64;  // w: second smoothing buffer
     float* u32; float* f32; float* r32; float* w32;
@@ -232,7 +237,37 @@ int launch_apply(sg_ctx* c, const Plan& pl, const void* U, int in_float, const d
 // the same for SG_DISC_P1 (called by launch_apply)
 int launch_apply_p1(sg_ctx* c, const Plan& pl, const void* U, int in_float, const double* R, void* Y,
                     int out_float, int ldu, int ldy, int ldr);
+// one four-colour cycle level, nu = 1 or 2 sweeps, each leg in one launch (sg_stream.hip); sps: the
+// level's stencils by column pairs, nx odd.  The cycle's own vectors lie in panels of C =
+// stream_modes() modes: panel c holds modes m0 .. m0 + C - 1, m0 = min(C c, width - C), node by node
+// (the last panel repeats modes of the one before when C does not divide the width).  f and the result
+// are node-major with the row strides given, or in panels where the stride is 0.
+// down: uo = nu forward sweeps from zero on f, fc = P^T (f - K uo).  up: uo = nu backward sweeps
+// from ui + P ec; uo must not overlap ui.
+int stream_modes(int is_float, int width);
+hipError_t stream_down(hipStream_t st, const float* sps, const float* f, int ldf, float* uo, float* fc, int nx, int width,
+                       int nu);
+hipError_t stream_down(hipStream_t st, const double* sps, const double* f, int ldf, double* uo, double* fc, int nx,
+                       int width, int nu);
+hipError_t stream_up(hipStream_t st, const float* sps, const float* f, int ldf, const float* ui, const float* ec, float* uo,
+                     int ldo, int nx, int width, int nu, bool p1);
+hipError_t stream_up(hipStream_t st, const double* sps, const double* f, int ldf, const double* ui, const double* ec,
+                     double* uo, int ldo, int nx, int width, int nu, bool p1);
+// the legs address rows of a segment and the stencils of a level in 32 bits: whether a level of nx x nx
+// nodes with row strides of at most ld elements fits
+inline bool stream_fits(int nx, int ld, size_t size) {
+    return (size_t)nx * ld * size * 80 < 0xFFFFFFFFull && (size_t)(nx + 1) * 10 * (nx + 3) * size < 0xFFFFFFFFull;
+}
+// elements of a block of `width` modes on N nodes, in panels or node-major
+inline size_t panel_elems(size_t N, int width) { return N * (width + 3); }
+// panel c of N nodes and pc modes each: offset of mode `col` of node 0 (nodes pc apart)
+__host__ __device__ inline size_t panel_offset(int col, int width, int pc, size_t N) {
+    const int c = col / pc, m0 = c * pc < width - pc ? c * pc : width - pc;
+    return (size_t)c * N * pc + (col - m0);
+}
 int launch_vcycle(sg_ctx* c, const void* f, int ldf, void* u, int ldu, int width, int is_float);
+// a level's device arrays made from its sten64: sten32, rdiag, stp, sps (nx odd) and cst (where allocated)
+int launch_level_setup(hipStream_t s, Level& lv);
 int launch_cast(hipStream_t s, const void* src, int src_float, int lds, void* dst, int dst_float, int ldd,
                 int rows, int width);
 int launch_fill(hipStream_t s, void* dst, int is_float, int ld, int rows, int width);

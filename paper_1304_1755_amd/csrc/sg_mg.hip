@@ -22,6 +22,9 @@
 // takes the mean of the coarse SW and NE corners instead of all four.
 //
 // Kernel forms by block width W (modes) and grid size:
+//   * four-colour cycles with one or two sweeps each way run the streaming legs of
+//     sg_stream.hip above the coarse part, two launches a level; the forms below
+//     serve other sweep counts and row strides too large for their addresses;
 //   * four-colour smoothing runs as row phases (one launch per row parity,
 //     both colours of a row): for W >= 32 a workgroup walks a row segment
 //     with lanes over modes (k_gs_rows; the first sweep from the zero start
@@ -496,10 +499,10 @@ __global__ void k_prolong_add(const T* __restrict__ ec, int ldc, T* __restrict__
 // u = Kinv f for every column; one block per column, double arithmetic
 template <typename T>
 __global__ void k_coarse(const double* __restrict__ kinv, const T* __restrict__ f, int ldf, T* __restrict__ u,
-                         int ldu, int Nc) {
+                         int ldu, int Nc, int pc) {
     extern __shared__ double fs[];
     SG_POISON_LDS(fs, Nc);
-    const int col = blockIdx.x;
+    const size_t col = pc ? panel_offset(blockIdx.x, gridDim.x, pc, Nc) : blockIdx.x;
     for (int i = threadIdx.x; i < Nc; i += blockDim.x) fs[i] = (double)f[(size_t)i * ldf + col];
     __syncthreads();
     for (int i = threadIdx.x; i < Nc; i += blockDim.x) {
@@ -1520,17 +1523,20 @@ constexpr int fused4_threads() { return sizeof(T) == 4 ? 1024 : 256; }
 template <typename T>
 __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_fused4(FusedLevels<T> fl, const double* __restrict__ kinv,
                                                         const T* __restrict__ fin, int ldf, T* __restrict__ uout,
-                                                        int ldu, int nu1, int nu2) {
+                                                        int ldu, int nu1, int nu2, int pc) {
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
     T* r = lds + fl.roff;
     SG_POISON_LDS(lds, fl.roff + fl.nx[0] * fl.nx[0]);
     const int col = blockIdx.x;
+    // the column's offset: blocks in panels of pc modes (node strides ldf = ldu = pc), or node-major
+    const size_t cin = pc ? panel_offset(col, gridDim.x, pc, fl.nx[0] * fl.nx[0]) : col;
+    const size_t cout = pc ? panel_offset(col, gridDim.x, pc, fl.nx[0] * fl.nx[0]) : col;
     const int L = fl.nlev - 1;
     {
         const int N0 = fl.nx[0] * fl.nx[0];
         T* f0 = lds + fl.off[0] + N0;
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[(size_t)i * ldf + col];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[cin + (size_t)i * ldf];
     }
     __syncthreads();
     OwnNodes<T> on;
@@ -1573,7 +1579,7 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_fused4(FusedLeve
     {
         const int N0 = fl.nx[0] * fl.nx[0];
         const T* u0 = lds + fl.off[0];
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) uout[(size_t)i * ldu + col] = u0[i];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) uout[cout + (size_t)i * ldu] = u0[i];
     }
 }
 
@@ -1746,11 +1752,14 @@ __host__ __device__ constexpr bool pad_cycle_size(int nx) { return nx == 63 || n
 template <typename T, bool LEX>
 __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T> pl, const double* __restrict__ kinv,
                                                                     const T* __restrict__ fin, int ldf,
-                                                                    T* __restrict__ uout, int ldu, int nu1, int nu2) {
+                                                                    T* __restrict__ uout, int ldu, int nu1, int nu2, int pc) {
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
     SG_POISON_LDS(lds, pl.roff + pl.nx[0] * pl.nx[0]);
     const int col = blockIdx.x;
+    // the column's offset: blocks in panels of pc modes (node strides ldf = ldu = pc), or node-major
+    const size_t cin = pc ? panel_offset(col, gridDim.x, pc, pl.nx[0] * pl.nx[0]) : col;
+    const size_t cout = pc ? panel_offset(col, gridDim.x, pc, pl.nx[0] * pl.nx[0]) : col;
     const int L = pl.nlev - 1;
     const int nx0 = pl.nx[0], N0 = nx0 * nx0;
     // zero every padded u: the border stays zero, the interiors are the zero initial guesses
@@ -1761,7 +1770,7 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T>
     }
     {
         T* f0 = lds + pl.foff[0];
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[(size_t)i * ldf + col];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[cin + (size_t)i * ldf];
     }
     __syncthreads();
     T* r = lds + pl.roff;
@@ -1853,7 +1862,53 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T>
         const T* u0 = lds + pl.uoff[0];
         for (int i = threadIdx.x; i < N0; i += blockDim.x) {
             const int y = i / nx0, x = i - y * nx0;
-            uout[(size_t)i * ldu + col] = u0[(y + 1) * (nx0 + 2) + x + 1];
+            uout[cout + (size_t)i * ldu] = u0[(y + 1) * (nx0 + 2) + x + 1];
+        }
+    }
+}
+
+// the arrays of a level that are made from its stencils, one thread per node: the float copy, the
+// reciprocal diagonals, the padded entries (stp), the column pairs (sps) and the colour order (cst)
+__global__ void __launch_bounds__(256) k_level_setup(const double* __restrict__ sten, int nx, float* __restrict__ s32,
+                                                     double* __restrict__ rd64, float* __restrict__ rd32,
+                                                     double* __restrict__ p64, float* __restrict__ p32,
+                                                     double* __restrict__ q64, float* __restrict__ q32,
+                                                     double* __restrict__ c64, float* __restrict__ c32) {
+    const int node = blockIdx.x * blockDim.x + threadIdx.x;
+    if (node >= nx * nx) return;
+    const int y = node / nx, x = node - y * nx;
+    double v[10];
+    float w[10];
+    for (int e = 0; e < 9; ++e) {
+        v[e] = sten[(size_t)node * 9 + e];
+        w[e] = (float)v[e];
+        s32[(size_t)node * 9 + e] = w[e];
+    }
+    v[9] = 1.0 / v[4];
+    w[9] = 1.0f / w[4];
+    rd64[node] = v[9];
+    rd32[node] = w[9];
+    for (int e = 0; e < 12; ++e) {
+        if (e < 10) p64[(size_t)node * 10 + e] = v[e];
+        p32[(size_t)node * 12 + e] = e < 10 ? w[e] : 0.0f;
+    }
+    if (q64) {
+        const size_t np = (nx + 3) / 2, row = (size_t)y * 20 * np, pair = x / 2, odd = x & 1;
+        for (int e = 0; e < 10; ++e) {
+            q64[row + (e * np + pair) * 2 + odd] = v[e];
+            q32[row + (e / 2 * np + pair) * 4 + (e & 1) * 2 + odd] = w[e];
+        }
+    }
+    if (c64) {
+        // colour q = (x odd when q is even) + (y odd when q < 2), the order of a forward sweep
+        const int q = (x & 1 ? 0 : 1) + (y & 1 ? 0 : 2);
+        int base = 0;
+        for (int c = 0; c < q; ++c) base += ((nx - ((c & 1) ^ 1) + 1) / 2) * ((nx - ((c >> 1) ^ 1) + 1) / 2);
+        const int px = (q & 1) ^ 1, py = (q >> 1) ^ 1;
+        const size_t i = base + (y - py) / 2 * ((nx - px + 1) / 2) + (x - px) / 2;
+        for (int e = 0; e < 12; ++e) {
+            if (e < 10) c64[i * 10 + e] = v[e];
+            c32[i * 12 + e] = e < 10 ? w[e] : 0.0f;
         }
     }
 }
@@ -1874,6 +1929,7 @@ struct LevelPtr<double> {
     static const double* rd(const Level& l) { return l.rdiag64; }
     static const double* cst(const Level& l) { return l.cst64; }
     static const double* stp(const Level& l) { return l.stp64; }
+    static const double* sps(const Level& l) { return l.sps64; }
 };
 template <>
 struct LevelPtr<float> {
@@ -1885,6 +1941,7 @@ struct LevelPtr<float> {
     static const float* rd(const Level& l) { return l.rdiag32; }
     static const float* cst(const Level& l) { return l.cst32; }
     static const float* stp(const Level& l) { return l.stp32; }
+    static const float* sps(const Level& l) { return l.sps32; }
 };
 
 template <typename T>
@@ -2051,15 +2108,30 @@ void launch_tile(bool down, int width, int ntiles, hipStream_t st, const T* stp,
                            ldo, nx, nu, ntx, ntiles, p1);
 }
 
+// the first level handled by the fused LDS kernel (-1: none fits, the coarsest is solved by k_coarse)
+template <typename T>
+int fused_level(const sg_ctx* c) {
+    for (size_t l = 0; l < c->levels.size(); ++l)
+        if (c->levels[l].nx <= fused_nx_max<T>()) return (int)l;
+    return -1;
+}
+
+// whether the streaming legs (sg_stream.hip) cycle the levels above the coarse part: four colours, one or
+// two sweeps each way, f and the result with row strides of at most ld elements
+template <typename T>
+bool use_stream(const sg_ctx* c, int ld) {
+    const int Lc = fused_level<T>(c);
+    return c->opt.colour_mode == SG_COLOUR_FOUR && (c->opt.nu1 == 1 || c->opt.nu1 == 2) &&
+           (c->opt.nu2 == 1 || c->opt.nu2 == 2) &&
+           (Lc >= 0 ? Lc : (int)c->levels.size() - 1) > 0 && stream_fits(c->levels[0].nx, ld, sizeof(T));
+}
+
 template <typename T>
 int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
     const Tile tl = tile_for(width);
     const int L = (int)c->levels.size() - 1;
     const bool p1 = c->hs.disc == SG_DISC_P1;  // transfer of the P1 triangulation
-    // first level handled by the fused LDS kernel (-1: none fits, coarsest solved by k_coarse)
-    int Lc = -1;
-    for (int l = 0; l <= L; ++l)
-        if (c->levels[l].nx <= fused_nx_max<T>()) { Lc = l; break; }
+    const int Lc = fused_level<T>(c);
     const int Ltop = Lc >= 0 ? Lc : L;  // levels above Ltop are cycled by separate launches
     // with row sweeps the finest level iterates in its own compact block (row
     // stride = width) and only the last post-smoothing sweep writes u0, whose
@@ -2068,10 +2140,13 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
     const bool compact0 = use_row_sweeps<T>(c, width) && Ltop > 0;
     T* const uc0 = compact0 ? LevelPtr<T>::u(c->levels[0]) : u0;
     const int ldc0 = compact0 ? width : ldu0;
+    // the streaming legs' own blocks lie in panels of pc modes
+    const bool stream = use_stream<T>(c, ldf0 > ldu0 ? ldf0 : ldu0);
+    const int pc = stream ? stream_modes(sizeof(T) == 4, width) : 0;
     auto fptr = [&](int l) -> const T* { return l == 0 ? f0 : LevelPtr<T>::f(c->levels[l]); };
-    auto fld = [&](int l) { return l == 0 ? ldf0 : width; };
+    auto fld = [&](int l) { return l == 0 ? ldf0 : pc ? pc : width; };
     auto uptr = [&](int l) -> T* { return l == 0 ? uc0 : LevelPtr<T>::u(c->levels[l]); };
-    auto uld = [&](int l) { return l == 0 ? ldc0 : width; };
+    auto uld = [&](int l) { return l == 0 ? ldc0 : pc ? pc : width; };
     // the coarse part: the fused LDS cycle from level Lc, or the coarsest solve at level L
     auto coarse_part = [&]() -> int {
         const bool lex = c->opt.colour_mode == SG_COLOUR_LEX;
@@ -2099,11 +2174,11 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
             if (lex)
                 hipLaunchKernelGGL((k_vcycle_pad<T, true>), dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, pl, (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc),
-                                   c->opt.nu1, c->opt.nu2);
+                                   c->opt.nu1, c->opt.nu2, pc);
             else
                 hipLaunchKernelGGL((k_vcycle_pad<T, false>), dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, pl, (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc),
-                                   c->opt.nu1, c->opt.nu2);
+                                   c->opt.nu1, c->opt.nu2, pc);
         } else if (Lc >= 0) {
             FusedLevels<T> fl{};
             fl.nlev = L - Lc + 1;
@@ -2126,7 +2201,7 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
             if (c->opt.colour_mode == SG_COLOUR_FOUR)
                 hipLaunchKernelGGL(k_vcycle_fused4<T>, dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, fl,
-                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2);
+                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2, pc);
             else
                 hipLaunchKernelGGL(k_vcycle_fused<T>, dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
                                    (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2,
@@ -2134,11 +2209,27 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
         } else {
             Level& lc = c->levels[L];
             hipLaunchKernelGGL(k_coarse<T>, dim3(width), dim3(256), (size_t)lc.N * sizeof(double), c->stream, c->kinv,
-                               fptr(L), fld(L), uptr(L), uld(L), lc.N);
+                               fptr(L), fld(L), uptr(L), uld(L), lc.N, pc);
         }
         return SG_OK;
     };
-    // Levels lt .. Ltop-1 are cycled by tiles (two launches per level): for
+    // a streamed or tiled level keeps its smoothed values in uptr(l) and writes its corrected ones to the
+    // level's second buffer (u0 on the finest level)
+    if (stream) {
+        for (int l = 0; l < Ltop; ++l)
+            if (stream_down(c->stream, LevelPtr<T>::sps(c->levels[l]), fptr(l), l == 0 ? ldf0 : 0, uptr(l),
+                            LevelPtr<T>::f(c->levels[l + 1]), c->levels[l].nx, width, c->opt.nu1) != hipSuccess)
+                return SG_EHIP;
+        if (int rc = coarse_part()) return rc;
+        for (int l = Ltop - 1; l >= 0; --l)
+            if (stream_up(c->stream, LevelPtr<T>::sps(c->levels[l]), fptr(l), l == 0 ? ldf0 : 0, uptr(l),
+                          l + 1 < Ltop ? LevelPtr<T>::u2(c->levels[l + 1]) : uptr(l + 1),
+                          l == 0 ? u0 : LevelPtr<T>::u2(c->levels[l]), l == 0 ? ldu0 : 0, c->levels[l].nx, width,
+                          c->opt.nu2, p1) != hipSuccess)
+                return SG_EHIP;
+        return hipGetLastError() == hipSuccess ? SG_OK : SG_EHIP;
+    }
+    // Without sweeps on one side, levels lt .. Ltop-1 are cycled by tiles (two launches per level): for
     // blocks of at most kTileMaxWidth modes every level with at most
     // kTileMaxWorkgroups (tile, mode) pairs, for blocks of at most kTileMidWidth
     // modes the grids of at most kTileMidNx nodes per side.  A
@@ -2240,6 +2331,18 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
 }
 
 }  // namespace
+
+int launch_level_setup(hipStream_t s, Level& lv) {
+    if (lv.sps64) {  // the zero row and the zero pairs
+        const size_t n = (size_t)(lv.nx + 1) * 10 * (lv.nx + 3);
+        if (hipMemsetAsync(lv.sps64, 0, n * sizeof(double), s) != hipSuccess ||
+            hipMemsetAsync(lv.sps32, 0, n * sizeof(float), s) != hipSuccess)
+            return SG_EHIP;
+    }
+    hipLaunchKernelGGL(k_level_setup, dim3((lv.N + 255) / 256), dim3(256), 0, s, lv.sten64, lv.nx, lv.sten32, lv.rdiag64,
+                       lv.rdiag32, lv.stp64, lv.stp32, lv.sps64, lv.sps32, lv.cst64, lv.cst32);
+    return hipGetLastError() == hipSuccess ? SG_OK : SG_EHIP;
+}
 
 int launch_vcycle(sg_ctx* c, const void* f, int ldf, void* u, int ldu, int width, int is_float) {
     int rc = is_float ? vcycle_t<float>(c, (const float*)f, ldf, (float*)u, ldu, width)
