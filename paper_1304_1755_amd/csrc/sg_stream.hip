@@ -269,15 +269,20 @@ struct Stencils {
             }
         }
     }
-    // before step k (row 2k in slot 2J): rows below it zero, rows 2k and 2k+1 in the ring, the next two loading
-    __device__ __forceinline__ void prime(int k) {
+    // before the first step k (row 2k in slot 0): rows 2k and 2k+1 into the ring, zeros for the three below
+    // them, the next two loading; `first` issues the walk's own first loads, so that all are in flight at once
+    template <typename F>
+    __device__ __forceinline__ void prime(int k, F first) {
         if constexpr (SH) {
             load(2 * k);
-            for (int i = threadIdx.x; i < kRing; i += blockDim.x) ring[i] = T(0);
-            meet();
+            first();
+            constexpr int below = 5 * NP * 128 * C;  // slots 5, 6, 7
+            for (int i = below + threadIdx.x; i < kRing; i += blockDim.x) ring[i] = T(0);
             store(0);
             load(2 * k + 2);
             meet();
+        } else {
+            first();
         }
     }
     // in step k: the rows of step k + 1 into the ring, those of step k + 2 loading
@@ -429,12 +434,13 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
     Stencils<T, SH> sten;
     sten.begin(sps, nx, s, ring);
     SG_POISON_LDS(ring, (Stencils<T, SH>::kRing));
-    sten.prime(k0);
     const Walked<T> wf = walked<T, M>(f, ldf, nx, 2 * k0, s.xe, s.xo, s);
     const Walked<T> wu = walked<T, M>((const T*)uo, 0, nx, 2 * s.Y0, s.xe, s.xo, s);
     const Walked<T> wc = walked<T, M>((const T*)fc, 0, nxc, s.Y0, min(X, nxc - 1), 0, s);
-    load_row<T, M>(wf, 2 * k0, fe[0]);
-    load_row<T, M>(wf, 2 * k0 + 1, fo[0]);
+    sten.prime(k0, [&] {
+        load_row<T, M>(wf, 2 * k0, fe[0]);
+        load_row<T, M>(wf, 2 * k0 + 1, fo[0]);
+    });
     auto step = [&](auto kj, int k) {
         constexpr int J = decltype(kj)::value, c = J & 1, p = c ^ 1, j1 = (J + 3) & 3, j2 = (J + 2) & 3, jn = (J + 1) & 3;
         sten.template feed<J>(k);
@@ -545,7 +551,6 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_up(const
     Stencils<T, SH> sten;
     sten.begin(sps, nx, s, ring);
     SG_POISON_LDS(ring, (Stencils<T, SH>::kRing));
-    sten.prime(k0);
     const Walked<T> wf = walked<T, M>(f, ldf, nx, 2 * k0, s.xe, s.xo, s);
     const Walked<T> wi = walked<T, M>(ui, 0, nx, 2 * k0, s.xe, s.xo, s);
     const Walked<T> wu = walked<T, M>((const T*)uo, ldo, nx, 2 * s.Y0, s.xe, s.xo, s);
@@ -559,7 +564,7 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_up(const
     };
     // doubles load the next step's rows late, where fewer registers are live
     constexpr bool kLate = sizeof(T) == 8;
-    issue(k0, fe[0], fo[0]);
+    sten.prime(k0, [&] { issue(k0, fe[0], fo[0]); });
     auto step = [&](auto kj, int k) {
         constexpr int J = decltype(kj)::value, c = J & 1, p = c ^ 1, j1 = (J + 3) & 3, j2 = (J + 2) & 3, jn = (J + 1) & 3;
         sten.template feed<J>(k);
@@ -639,26 +644,33 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_up(const
 
 struct StreamShape {
     int ns, seg, nseg;
+    bool shared;  // workgroups of four chunks share the stencils
 };
 
 // Long segments throw less away (4 of seg + 4 steps), short ones give a launch
 // enough wavefronts: the longest that leaves kStreamWaves of them (at 511^2, W = 126,
-// float: 485 us a cycle with 512, 468 with 1024, 444 with 2048, 538 with 4096).
+// float: 485 us a cycle with 512, 468 with 1024, 444 with 2048, 538 with 4096), and one
+// coarse row only where that still gives every second CU at most one workgroup (at
+// 127^2, double: W = 1 51 -> 48 us, W = 10 60 -> 56, but W = 35 68 -> 76).
+// Wavefronts share their stencils from three chunks on, and in launches of at most a
+// workgroup per CU, where a second and third wavefront that only loads shortens
+// the steps (127^2, double, W = 1: 60 -> 51 us, W = 4: 73 -> 57; 511^2, float, W = 1: 80 -> 84).
 constexpr int kStreamWaves = 2048;
 StreamShape stream_shape(int nx, int nch) {
-    const int nxc = (nx - 1) / 2;
-    StreamShape h{strip_count(nx), 32, 0};
+    const int nxc = (nx - 1) / 2, groups = (nch + kShWaves - 1) / kShWaves;
+    StreamShape h{strip_count(nx), 32, 0, false};
     while (h.seg > 2 && (long)nch * h.ns * ((nxc + h.seg - 1) / h.seg) < kStreamWaves) h.seg >>= 1;
+    if (h.seg == 2 && (long)groups * h.ns * nxc <= 128) h.seg = 1;
     h.nseg = (nxc + h.seg - 1) / h.seg;
+    h.shared = nch >= 3 || h.ns * h.nseg <= 256;
     return h;
 }
 
-// From three chunks on, workgroups of four chunks share the stencils.
 template <typename T, int M, int NU>
 hipError_t down_m(hipStream_t st, const T* sps, const T* f, int ldf, T* uo, T* fc, int nx, int width) {
     const int nch = (width + M - 1) / M;
     const StreamShape h = stream_shape(nx, nch);
-    if (nch >= 3)
+    if (h.shared)
         hipLaunchKernelGGL((k_stream_down<T, M, NU, true>), dim3((nch + kShWaves - 1) / kShWaves * h.ns * h.nseg), dim3(256),
                            0, st, sps, f, ldf, uo, fc, nx, width, nch, h.ns, h.seg, h.nseg);
     else
@@ -672,7 +684,7 @@ hipError_t up_m(hipStream_t st, const T* sps, const T* f, int ldf, const T* ui, 
                 int width) {
     const int nch = (width + M - 1) / M;
     const StreamShape h = stream_shape(nx, nch);
-    if (nch >= 3)
+    if (h.shared)
         hipLaunchKernelGGL((k_stream_up<T, M, NU, P1T, true>), dim3((nch + kShWaves - 1) / kShWaves * h.ns * h.nseg),
                            dim3(256), 0, st, sps, f, ldf, ui, ec, uo, ldo, nx, width, nch, h.ns, h.seg, h.nseg);
     else
