@@ -940,6 +940,8 @@ int sg_setup(const sg_options* opt, const double* a0_nodal, const double* kl_amp
         if ((lv.nx & 1) && ((rc = dalloc(c, &lv.sps64, pairs)) || (rc = dalloc(c, &lv.sps32, pairs)))) return fail(rc);
         if (lv.nx <= kLdsCycleMaxNx && ((rc = dalloc(c, &lv.cst64, nn * 10)) || (rc = dalloc(c, &lv.cst32, nn * 12))))
             return fail(rc);
+        const size_t nlex = opt->colour_mode == SG_COLOUR_LEX ? lex_setup_elems(lv.nx) : 0;
+        if (nlex && ((rc = dalloc(c, &lv.lex64, nlex)) || (rc = dalloc(c, &lv.lex32, nlex)))) return fail(rc);
         if ((rc = launch_level_setup(c->stream, lv))) {
             set_error("sg_setup: level setup launch failed");
             return fail(rc);

@@ -159,6 +159,10 @@ struct Level {
     // pair adjacent; in float two coefficients of a pair share a 16-byte piece
     double* sps64;
     float* sps32;
+    // coefficients of the lexicographic sweeps front by front, forward then backward (contexts with
+    // SG_COLOUR_LEX, grids of at most 63 nodes per side)
+    double* lex64;
+    float* lex32;
     // work buffers, capacity N x P
     double* u64; double* f64; double* r64; double* w64;  // w: second smoothing buffer
     float* u32; float* f32; float* r32; float* w32;
@@ -266,8 +270,9 @@ __host__ __device__ inline size_t panel_offset(int col, int width, int pc, size_
     return (size_t)c * N * pc + (col - m0);
 }
 int launch_vcycle(sg_ctx* c, const void* f, int ldf, void* u, int ldu, int width, int is_float);
-// a level's device arrays made from its sten64: sten32, rdiag, stp, sps (nx odd) and cst (where allocated)
+// a level's device arrays made from its sten64: sten32, rdiag, stp, and where allocated sps (nx odd), cst, lex
 int launch_level_setup(hipStream_t s, Level& lv);
+size_t lex_setup_elems(int nx);  // elements of lex64 and lex32, 0 on grids that have none
 int launch_cast(hipStream_t s, const void* src, int src_float, int lds, void* dst, int dst_float, int ldd,
                 int rows, int width);
 int launch_fill(hipStream_t s, void* dst, int is_float, int ld, int rows, int width);

@@ -1087,6 +1087,7 @@ struct FusedLevels {
     int off[kMaxFusedLevels];       // LDS element offset of u_l (f_l follows at off + N_l)
     const T* sten[kMaxFusedLevels];
     const T* rdiag[kMaxFusedLevels];  // reciprocals of the stencil diagonals
+    const T* lex[kMaxFusedLevels];    // lexicographic coefficients, forward then backward
     int roff;                       // LDS element offset of the residual / staging array
     int p1;                         // transfer of the P1 triangulation (else bilinear)
 };
@@ -1123,151 +1124,247 @@ __device__ __forceinline__ void lex_front(int d, int nx, int& ylo, int& yhi) {
     yhi = min(nx - 1, d / 2);
 }
 
-// Lexicographic sweeps by one wavefront, for grids of at most kLexWaveMaxNx
-// nodes per side held in LDS (u and f, nx x nx each): lane y owns grid row y,
-// and at front d every lane relaxes node (d - 2y, y) of its row.  One
-// wavefront needs no workgroup barrier between fronts (the LDS operations of a
-// wavefront complete in issue order; the wavefront-scope fences keep the
-// compiler from moving LDS accesses across a front).  Each lane loads the
-// stencils and right-hand sides of its next kLexAhead nodes ahead of time
-// (f does not change during a sweep), and reads the eight
-// neighbours at clamped addresses (zero outside the grid) so that the reads
-// carry no branches and are issued together.  The relaxation sums the
-// neighbours in two chains (same values as k_gs_lex up to rounding).
-constexpr int kLexWaveMaxNx = 63;  // at most 64 rows, one per lane
-constexpr int kLexAhead = 8;
+// Lexicographic sweeps by one wavefront, for grids of at most kLexMaxNx nodes per
+// side: lane t owns grid row t (a backward sweep is a forward one on the grid
+// turned by 180 degrees, row t then counts from the top), and at front d every
+// lane relaxes the node (d - 2t, t) of its row.  Of the node's four new
+// neighbours the west one is the lane's own last value, and the three below it
+// are the last three values of lane t - 1, one DPP wave shift a front.  So a front
+// depends on the one before through one shift and two multiply-adds.  What the
+// sweep does not change -- the coefficients (divided by the diagonal, front by
+// front, zero where a lane has no node or a neighbour lies outside the grid), the
+// right-hand side, the old east and north-east values -- seven more wavefronts of
+// the workgroup bring into LDS, a front each at a time, and hold the next
+// kLexAhead fronts each on their way (a front takes less time than a load).
+//
+// What bounds it: 3 nx - 2 dependent fronts, about 0.18 us each; the chain itself
+// (a shift and two multiply-adds) would allow a third of that.  A 63^2 sweep of 126
+// columns takes 34 us, 70 with the neighbours read from LDS at every front and the
+// coefficients from a node-ordered array a cache line per lane; the left GMRES solve of
+// the 65 x 65 problem with the 2 x 2 split went from 36.9 to 19.2 ms with this and the
+// coupling of k_split_couple.
+constexpr int kLexMaxNx = 63;  // at most 64 rows, one per lane
+constexpr int kLexChunk = 7;   // fronts in LDS at a time, one per loading wavefront
+constexpr int kLexAhead = 6;   // chunks on their way
+constexpr int kLexThreads = 64 * (kLexChunk + 1);
+constexpr int kLexPieces = 5;  // pairs of coefficients: rd E | N NE | NW S | SW W | SE 0
+constexpr int kLexRing = 3 * kLexChunk * (kLexPieces + 1) * 128;  // elements of the LDS ring: the chunk swept, the next, the one being written
+// elements of the coefficients of one direction
+__host__ __device__ constexpr int lex_chunks(int nx) { return (3 * nx - 2 + kLexChunk - 1) / kLexChunk; }
+__host__ __device__ constexpr size_t lex_elems(int nx) { return (size_t)lex_chunks(nx) * kLexChunk * kLexPieces * 128; }
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+__device__ __forceinline__ float lane_below(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_below(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lex_fma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double lex_fma(double a, double b, double c) { return fma(a, b, c); }
+
+// LDS accesses done and every wavefront of the workgroup here (global loads stay in flight)
+__device__ __forceinline__ void lds_meet() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __asm__ __volatile__("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __asm__ __volatile__("" ::: "memory");
 }
 
-template <typename T>
-__device__ __forceinline__ void wave_lex_sweeps(const T* __restrict__ sten, const T* __restrict__ rdiag, T* us,
-                                                const T* fs, int nx, bool reverse, int nu) {
-    const int y = threadIdx.x & 63;
-    const int nd = 3 * (nx - 1) + 1;
-    for (int sweep = 0; sweep < nu; ++sweep) {
-        auto node_at = [&](int di) -> int {
-            const int d = reverse ? nd - 1 - di : di, x = d - 2 * y;
-            return (di < nd && y < nx && x >= 0 && x < nx) ? y * nx + x : -1;
+// One sweep, called by all wavefronts of a workgroup of at least kLexThreads; the first one sweeps, the next
+// seven load.  get_f(d), get_e(d, x, y): the calling lane's right-hand side at front d, and its old value
+// x columns east and y rows north of the node of front d, both zero where there is none; put(d, v): the
+// lane's new value at front d, to be dropped where it has no node.  Old values are read before the
+// front that overwrites them.
+template <typename T, typename F, typename E, typename S>
+__device__ __forceinline__ void lex_sweep(const T* __restrict__ lex, int nx, T* ring, F get_f, E get_e, S put) {
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    constexpr int NP = kLexPieces + 1, NQ = kLexChunk * NP;  // pieces of a front, of a chunk
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nc = lex_chunks(nx);
+    V2* const r2 = (V2*)ring + lane;
+    if (wv > kLexChunk) {
+        for (int c = 0; c <= nc; ++c) lds_meet();
+    } else if (wv > 0) {
+        const V2* c2 = (const V2*)lex + lane;
+        V2 a[kLexAhead][NP];
+        auto load = [&](V2 (&v)[NP], int chunk) {
+            // past the end the last chunk again: a skipped load would make every wait one for all loads
+            const int d = min(chunk, nc - 1) * kLexChunk + wv - 1;
+#pragma unroll
+            for (int p = 0; p < kLexPieces - 1; ++p) v[p] = c2[(d * kLexPieces + p) * 64];
+            // one half only: a load of the pair would have to arrive before its other half is replaced
+            v[kLexPieces - 1].x = ((const T*)(c2 + (d * kLexPieces + kLexPieces - 1) * 64))[0];
+            v[kLexPieces - 1].y = get_e(d, 1, 1);
+            v[kLexPieces].x = get_f(d);
+            v[kLexPieces].y = get_e(d, 1, 0);
         };
-        T st[kLexAhead][9], rd[kLexAhead], rf[kLexAhead];
-        auto fetch = [&](int j, int di) {
-            const int node = max(node_at(di), 0);
+        auto store = [&](const V2 (&v)[NP], int chunk) {
 #pragma unroll
-            for (int t = 0; t < 9; ++t) st[j][t] = sten[(size_t)node * 9 + t];
-            rd[j] = rdiag[node];
-            rf[j] = fs[node];
+            for (int p = 0; p < NP; ++p) r2[((chunk % 3) * NQ + (wv - 1) * NP + p) * 64] = v[p];
         };
 #pragma unroll
-        for (int j = 0; j < kLexAhead; ++j) fetch(j, j);
-        for (int di0 = 0; di0 < nd; di0 += kLexAhead) {
+        for (int i = 0; i < kLexAhead; ++i) load(a[i], i);
+        store(a[0], 0);
+        load(a[0], kLexAhead);
+        store(a[1], 1);
+        load(a[1], kLexAhead + 1);
+        lds_meet();
+        for (int c0 = 0; c0 < nc; c0 += kLexAhead) {
 #pragma unroll
-            for (int j = 0; j < kLexAhead; ++j) {
-                const int node = node_at(di0 + j);
-                if (node >= 0) {
-                    const int x = node - y * nx;
-                    T v[9];
-#pragma unroll
-                    for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-                        for (int dx = -1; dx <= 1; ++dx) {
-                            const int xx = x + dx, yy = y + dy, t = (dy + 1) * 3 + (dx + 1);
-                            const bool in = xx >= 0 && xx < nx && yy >= 0 && yy < nx;
-                            const T w = us[in ? yy * nx + xx : node];
-                            v[t] = in ? w : T(0);
-                        }
-                    // two partial sums (rows below and above the node) shorten the dependent chain
-                    T lo = rf[j] - st[j][0] * v[0], hi = st[j][6] * v[6];
-                    lo -= st[j][1] * v[1];
-                    hi += st[j][7] * v[7];
-                    lo -= st[j][2] * v[2];
-                    hi += st[j][8] * v[8];
-                    lo -= st[j][3] * v[3];
-                    hi += st[j][5] * v[5];
-                    us[node] = (lo - hi) * rd[j];
-                }
-                fetch(j, di0 + j + kLexAhead);
-                wave_sync();
+            for (int i = 0; i < kLexAhead; ++i) {
+                const int c = c0 + i;
+                if (c >= nc) break;
+                store(a[(i + 2) % kLexAhead], c + 2);
+                load(a[(i + 2) % kLexAhead], c + 2 + kLexAhead);
+                lds_meet();
             }
+        }
+    } else {
+        // v: last value; s, sw: lane t - 1's values of two and three fronts back; n, nw: old north ones
+        T v = T(0), s = T(0), sw = T(0), nw = T(0);
+        T n = get_e(-1, 1, 1);
+        lds_meet();
+        constexpr int A = 2;  // fronts read ahead
+        V2 w[kLexChunk][NP];
+#pragma unroll
+        for (int j = 0; j < A; ++j)
+#pragma unroll
+            for (int i = 0; i < NP; ++i) w[j][i] = r2[(j * NP + i) * 64];
+        for (int c = 0; c < nc; ++c) {
+            // front j + A is read while front j is relaxed; past the chunk it is one of the next
+            // (after the last chunk: values of an old one, not used)
+            const V2* here = r2 + (c % 3) * NQ * 64;
+            const V2* next = r2 + ((c + 1) % 3) * NQ * 64;
+#pragma unroll
+            for (int j = 0; j < kLexChunk; ++j) {
+#pragma unroll
+                for (int i = 0; i < NP; ++i)
+                    w[(j + A) % kLexChunk][i] = j + A < kLexChunk ? here[((j + A) * NP + i) * 64] : next[((j + A - kLexChunk) * NP + i) * 64];
+                __builtin_amdgcn_sched_barrier(0);
+                const V2* k = w[j];
+                const T ne = k[4].y;
+                T p = k[0].x * k[5].x;
+                p = lex_fma(-k[0].y, k[5].y, p);
+                T q = k[1].x * n;
+                q = lex_fma(k[1].y, ne, q);
+                q = lex_fma(k[2].x, nw, q);
+                p = lex_fma(-k[2].y, s, p);
+                p = lex_fma(-k[3].x, sw, p);
+                p -= q;
+                p = lex_fma(-k[3].y, v, p);
+                const T se = lane_below(v);
+                v = lex_fma(-k[4].x, se, p);
+                put(c * kLexChunk + j, v);
+                sw = s;
+                s = se;
+                nw = n;
+                n = ne;
+            }
+            lds_meet();
         }
     }
 }
 
-// One lexicographic sweep per right-hand-side column, one wavefront each:
-// the column sits in LDS inside a border of zeros ((nx+2)^2 values), so a
-// node's eight neighbours are read at fixed offsets from one address with no
-// bounds tests, and f, the stencils and the reciprocal diagonals (none of
-// which the sweep changes) are loaded from global memory kLexAhead fronts
-// ahead.  zero_start: the column starts from zero (not read).  Same fronts
-// and arithmetic as wave_lex_sweeps.
-template <typename T>
-__global__ void __launch_bounds__(64) k_lex_wave(const T* __restrict__ sten, const T* __restrict__ rdiag, T* u,
-                                                 int ldu, const T* __restrict__ f, int ldf, int nx, int reverse,
-                                                 int zero_start) {
-    extern __shared__ char smem_raw[];
-    T* us = (T*)smem_raw;
-    const int col = blockIdx.x, pw = nx + 2, N = nx * nx;
-    SG_POISON_LDS(us, pw * pw);
-    for (int i = threadIdx.x; i < pw * pw; i += 64) {
-        const int py = i / pw, px = i - py * pw;
-        const bool in = px >= 1 && px <= nx && py >= 1 && py <= nx;
-        us[i] = (in && !zero_start) ? u[(size_t)((py - 1) * nx + px - 1) * ldu + col] : T(0);
-    }
-    wave_sync();
-    const int y = threadIdx.x;
-    const int nd = 3 * (nx - 1) + 1;
-    auto x_at = [&](int di) -> int { return (reverse ? nd - 1 - di : di) - 2 * y; };
-    auto live = [&](int di, int x) { return di < nd && y < nx && x >= 0 && x < nx; };
-    T st[kLexAhead][9], rd[kLexAhead], rf[kLexAhead];
-    auto fetch = [&](int j, int di) {
-        const int x = x_at(di);
-        const int node = live(di, x) ? y * nx + x : 0;
-#pragma unroll
-        for (int t = 0; t < 9; ++t) st[j][t] = sten[(size_t)node * 9 + t];
-        rd[j] = rdiag[node];
-        rf[j] = f[(size_t)node * ldf + col];
+// One sweep per right-hand-side column in global memory, a workgroup each, u in place: a lane writes its
+// own row only.  ZERO: u holds nothing yet (the old values are zero).  Values a lane does not have are
+// fetched from past the buffer's end, which gives zero, and stored there, which drops them.
+template <typename T, bool ZERO>
+__global__ void __launch_bounds__(kLexThreads) k_lex_sweep(const T* __restrict__ lex, T* u, int ldu, const T* f, int ldf, int nx,
+                                                   int reverse) {
+    __shared__ __attribute__((aligned(16))) T ring[kLexRing];
+    SG_POISON_LDS(ring, kLexRing);
+    const int t = threadIdx.x & 63, N = nx * nx, col = blockIdx.x;
+    const __amdgpu_buffer_rsrc_t ub =
+        __builtin_amdgcn_make_buffer_rsrc(u + col, 0, (unsigned)(((N - 1) * (size_t)ldu + 1) * sizeof(T)), 0x00020000);
+    const __amdgpu_buffer_rsrc_t fb =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(f + col), 0, (unsigned)(((N - 1) * (size_t)ldf + 1) * sizeof(T)), 0x00020000);
+    // byte offset of node (d - 2t, t) of the (turned) grid: start + d * step
+    const int first = t * nx - 2 * t;
+    const unsigned fs = ldf * (unsigned)sizeof(T) * (reverse ? -1 : 1), us = ldu * (unsigned)sizeof(T) * (reverse ? -1 : 1);
+    const unsigned f0 = (unsigned)(reverse ? N - 1 : 0) * (ldf * (unsigned)sizeof(T)) + (unsigned)first * fs;
+    const unsigned u0 = (unsigned)(reverse ? N - 1 : 0) * (ldu * (unsigned)sizeof(T)) + (unsigned)first * us;
+    constexpr unsigned kNoNode = 0x80000000u;  // past the end of every buffer (launch_lex)
+    auto inside = [&](int x, int y) { return (unsigned)y < (unsigned)nx && (unsigned)x < (unsigned)nx; };
+    typedef unsigned U2 __attribute__((ext_vector_type(2)));
+    auto load = [&](const __amdgpu_buffer_rsrc_t& b, unsigned off) -> T {
+        if constexpr (sizeof(T) == 4)
+            return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0));
+        else
+            return __builtin_bit_cast(double, (U2)__builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
     };
-#pragma unroll
-    for (int j = 0; j < kLexAhead; ++j) fetch(j, j);
-    for (int di0 = 0; di0 < nd; di0 += kLexAhead) {
-#pragma unroll
-        for (int j = 0; j < kLexAhead; ++j) {
-            const int x = x_at(di0 + j);
-            if (live(di0 + j, x)) {
-                // b: the south-west neighbour of node (x, y) in the padded grid
-                T* b = us + y * pw + x;
-                const T vSW = b[0], vS = b[1], vSE = b[2], vW = b[pw], vE = b[pw + 2];
-                const T vNW = b[2 * pw], vN = b[2 * pw + 1], vNE = b[2 * pw + 2];
-                T lo = rf[j] - st[j][0] * vSW, hi = st[j][6] * vNW;
-                lo -= st[j][1] * vS;
-                hi += st[j][7] * vN;
-                lo -= st[j][2] * vSE;
-                hi += st[j][8] * vNE;
-                lo -= st[j][3] * vW;
-                hi += st[j][5] * vE;
-                b[pw + 1] = (lo - hi) * rd[j];
-            }
-            fetch(j, di0 + j + kLexAhead);
-            wave_sync();
-        }
+    lex_sweep<T>(
+        lex, nx, ring, [&](int d) -> T { return load(fb, inside(d - 2 * t, t) ? f0 + (unsigned)d * fs : kNoNode); },
+        [&](int d, int x, int y) -> T {
+            if (ZERO) return T(0);
+            return load(ub, inside(d - 2 * t + x, t + y) ? u0 + (unsigned)(d + x + y * nx) * us : kNoNode);
+        },
+        [&](int d, T v) {
+            const unsigned off = inside(d - 2 * t, t) ? u0 + (unsigned)d * us : kNoNode;
+            if constexpr (sizeof(T) == 4)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ub, off, 0, 0);
+            else
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), ub, off, 0, 0);
+        });
+}
+
+// nu sweeps by the whole workgroup on a grid in LDS, rows `pitch` apart
+template <typename T>
+__device__ __forceinline__ void lds_lex(const T* __restrict__ lex, T* ring, T* u, int pitch, const T* f, int nx,
+                                        bool reverse, int nu) {
+    const int t = threadIdx.x & 63;
+    auto inside = [&](int x, int y) { return (unsigned)y < (unsigned)nx && (unsigned)x < (unsigned)nx; };
+    auto at = [&](int x, int y, int p) { return reverse ? (nx - 1 - y) * p + nx - 1 - x : y * p + x; };
+    for (int sweep = 0; sweep < nu; ++sweep)
+        lex_sweep<T>(
+            lex, nx, ring, [&](int d) -> T { const int x = d - 2 * t; return inside(x, t) ? f[at(x, t, nx)] : T(0); },
+            [&](int d, int x, int y) -> T {
+                x += d - 2 * t;
+                y += t;
+                return inside(x, y) ? u[at(x, y, pitch)] : T(0);
+            },
+            [&](int d, T v) { const int x = d - 2 * t; if (inside(x, t)) u[at(x, t, pitch)] = v; });
+}
+
+// the coefficients of lex_sweep, forward then backward, from a level's stencils: one workgroup of 64
+// lanes per front and direction
+__global__ void __launch_bounds__(64) k_lex_setup(const double* __restrict__ sten, int nx, double* __restrict__ l64,
+                                                  float* __restrict__ l32) {
+    const int nf = lex_chunks(nx) * kLexChunk, reverse = blockIdx.x >= nf, d = blockIdx.x - reverse * nf, t = threadIdx.x;
+    const int x = d - 2 * t;
+    const bool in = t < nx && x >= 0 && x < nx;
+    double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (in) {
+        const int node = t * nx + x;
+        const double* s9 = sten + (size_t)(reverse ? nx * nx - 1 - node : node) * 9;
+        auto c = [&](int dx, int dy) -> double {
+            const int xx = x + dx, yy = t + dy, e = (dy + 1) * 3 + dx + 1;
+            return xx >= 0 && xx < nx && yy >= 0 && yy < nx ? s9[reverse ? 8 - e : e] / s9[4] : 0.0;
+        };
+        v[0] = 1.0 / s9[4];
+        v[1] = c(1, 0);
+        v[2] = c(0, 1);
+        v[3] = c(1, 1);
+        v[4] = c(-1, 1);
+        v[5] = c(0, -1);
+        v[6] = c(-1, -1);
+        v[7] = c(-1, 0);
+        v[8] = c(1, -1);
     }
-    for (int i = threadIdx.x; i < N; i += 64) {
-        const int py = i / nx, px = i - py * nx;
-        u[(size_t)i * ldu + col] = us[(py + 1) * pw + px + 1];
+    const size_t at = reverse * lex_elems(nx) + (size_t)d * kLexPieces * 128;
+    for (int e = 0; e < 10; ++e) {
+        const size_t i = at + (e / 2) * 128 + t * 2 + (e & 1);
+        l64[i] = v[e];
+        l32[i] = (float)v[e];
     }
 }
 
 // mode 0: four colours; 1: red/black from start-of-colour values; 2: lexicographic
-template <typename T>
-__device__ void lds_smooth(const T* __restrict__ st, const T* __restrict__ rdiag, T* u, const T* f, T* stage, int nx,
-                           int mode, bool reverse,
-                           int nu) {
-    if (mode == 2) {
-        // the first wavefront sweeps (every fused grid has at most 63 rows); the others wait
-        if (threadIdx.x < 64) wave_lex_sweeps<T>(st, rdiag, u, f, nx, reverse, nu);
+template <typename T, bool LEX>
+__device__ void lds_smooth(const T* __restrict__ st, const T* __restrict__ rdiag, const T* __restrict__ lex, T* u,
+                           const T* f, T* stage, int nx, int mode, bool reverse, int nu, T* ring) {
+    if constexpr (LEX) {
+        // the first wavefront sweeps (every fused grid has at most 63 rows)
+        lds_lex<T>(lex + (reverse ? lex_elems(nx) : 0), ring, u, nx, f, nx, reverse, nu);
         __syncthreads();
         return;
     }
@@ -1341,10 +1438,11 @@ __global__ void __launch_bounds__(256) k_gs_lex(const T* __restrict__ sten, cons
     }
 }
 
-template <typename T>
+template <typename T, bool LEX>
 __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const double* __restrict__ kinv,
                                                       const T* __restrict__ fin, int ldf, T* __restrict__ uout,
                                                       int ldu, int nu1, int nu2, int mode) {
+    __shared__ __attribute__((aligned(16))) T ring[LEX ? kLexRing : 1];
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
     T* r = lds + fl.roff;
@@ -1363,7 +1461,7 @@ __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const d
         T* f = u + N;
         for (int i = threadIdx.x; i < N; i += blockDim.x) u[i] = T(0);
         __syncthreads();
-        lds_smooth<T>(fl.sten[l], fl.rdiag[l], u, f, r, nx, mode, false, nu1);
+        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, mode, false, nu1, ring);
         // residual r = f - K u
         for (int node = threadIdx.x; node < N; node += blockDim.x) {
             const int y = node / nx, x = node - y * nx;
@@ -1415,7 +1513,7 @@ __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const d
             u[node] += prolong_value<T>([&](int X, int Y) { return ec[Y * nxc + X]; }, nxc, x, y, fl.p1 != 0);
         }
         __syncthreads();
-        lds_smooth<T>(fl.sten[l], fl.rdiag[l], u, f, r, nx, mode, true, nu2);
+        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, mode, true, nu2, ring);
     }
     {
         const int N0 = fl.nx[0] * fl.nx[0];
@@ -1599,8 +1697,7 @@ struct PadLevels {
     int uoff[kMaxFusedLevels];      // LDS element offset of the padded u_l
     int foff[kMaxFusedLevels];      // LDS element offset of f_l (nx^2 values)
     const T* cst[kMaxFusedLevels];  // colour-ordered stencils of the levels above the coarsest
-    const T* sten[kMaxFusedLevels];   // node-ordered stencils and reciprocal diagonals (lexicographic sweeps)
-    const T* rdiag[kMaxFusedLevels];
+    const T* lex[kMaxFusedLevels];  // lexicographic coefficients, forward then backward
     int roff;                       // LDS element offset of the residual of the top level
     int p1;                         // transfer of the P1 triangulation (else bilinear)
 };
@@ -1687,53 +1784,6 @@ __device__ __forceinline__ void pad_smooth(const OwnPad<T>& on, T* u, const T* f
         }
 }
 
-// nu lexicographic sweeps (backward when reverse) on the padded grid by the
-// calling wavefront (the first of the workgroup; the caller meets the others
-// at a barrier afterwards): the fronts of k_lex_wave with the neighbour
-// offsets compile-time immediates, the stencils and reciprocal diagonals
-// loaded from global memory and f from LDS kLexAhead fronts ahead
-template <typename T, int NX>
-__device__ __forceinline__ void pad_lex(const T* __restrict__ sten, const T* __restrict__ rdiag, T* u, const T* f,
-                                        bool reverse, int nu) {
-    constexpr int PW = NX + 2;
-    constexpr int ND = 3 * (NX - 1) + 1;
-    const int y = threadIdx.x & 63;
-    for (int sweep = 0; sweep < nu; ++sweep) {
-        auto x_at = [&](int di) -> int { return (reverse ? ND - 1 - di : di) - 2 * y; };
-        auto live = [&](int di, int x) { return di < ND && y < NX && x >= 0 && x < NX; };
-        T st[kLexAhead][9], rd[kLexAhead], rf[kLexAhead];
-        auto fetch = [&](int j, int di) {
-            const int x = x_at(di);
-            const int node = live(di, x) ? y * NX + x : 0;
-#pragma unroll
-            for (int t = 0; t < 9; ++t) st[j][t] = sten[(size_t)node * 9 + t];
-            rd[j] = rdiag[node];
-            rf[j] = f[node];
-        };
-#pragma unroll
-        for (int j = 0; j < kLexAhead; ++j) fetch(j, j);
-        for (int di0 = 0; di0 < ND; di0 += kLexAhead) {
-#pragma unroll
-            for (int j = 0; j < kLexAhead; ++j) {
-                const int x = x_at(di0 + j);
-                if (live(di0 + j, x)) {
-                    T* b = u + y * PW + x;  // the south-west neighbour of (x, y)
-                    T lo = rf[j] - st[j][0] * b[0], hi = st[j][6] * b[2 * PW];
-                    lo -= st[j][1] * b[1];
-                    hi += st[j][7] * b[2 * PW + 1];
-                    lo -= st[j][2] * b[2];
-                    hi += st[j][8] * b[2 * PW + 2];
-                    lo -= st[j][3] * b[PW];
-                    hi += st[j][5] * b[PW + 2];
-                    b[PW + 1] = (lo - hi) * rd[j];
-                }
-                fetch(j, di0 + j + kLexAhead);
-                wave_sync();
-            }
-        }
-    }
-}
-
 // calls f(integral_constant<int, nx>) for the level sizes of the padded cycle
 template <typename F>
 __device__ __forceinline__ void with_pad_nx(int nx, F&& f) {
@@ -1749,10 +1799,19 @@ __device__ __forceinline__ void with_pad_nx(int nx, F&& f) {
 
 __host__ __device__ constexpr bool pad_cycle_size(int nx) { return nx == 63 || nx == 31 || nx == 15 || nx == 7 || nx == 3; }
 
+// threads of a workgroup: one per node of a colour of the largest grid, and enough to sweep lexicographically
 template <typename T, bool LEX>
-__global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T> pl, const double* __restrict__ kinv,
+constexpr int pad_threads() {
+    constexpr int four = fused4_threads<T>();
+    return LEX && (four < kLexThreads) ? kLexThreads : four;
+}
+
+template <typename T, bool LEX>
+__global__ void __launch_bounds__((pad_threads<T, LEX>())) k_vcycle_pad(PadLevels<T> pl, const double* __restrict__ kinv,
                                                                     const T* __restrict__ fin, int ldf,
                                                                     T* __restrict__ uout, int ldu, int nu1, int nu2, int pc) {
+    __shared__ __attribute__((aligned(16))) T ring[LEX ? kLexRing : 1];
+    SG_POISON_LDS(ring, LEX ? kLexRing : 1);
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
     SG_POISON_LDS(lds, pl.roff + pl.nx[0] * pl.nx[0]);
@@ -1775,7 +1834,15 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T>
     __syncthreads();
     T* r = lds + pl.roff;
     OwnPad<T> on;
+    // lexicographic sweeps, outside the code of each level size
+    auto lex = [&](int l, bool reverse, int nu) {
+        const int nx = pl.nx[l];
+        lds_lex<T>(pl.lex[l] + (reverse ? lex_elems(nx) : 0), ring, lds + pl.uoff[l] + nx + 3, nx + 2, lds + pl.foff[l], nx,
+                   reverse, nu);
+        __syncthreads();
+    };
     for (int l = 0; l < L; ++l) {
+        if constexpr (LEX) lex(l, false, nu1);
         with_pad_nx(pl.nx[l], [&](auto knx) __attribute__((always_inline)) {
             constexpr int NX = decltype(knx)::value;
             constexpr int NXC = (NX - 1) / 2;
@@ -1787,12 +1854,7 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T>
             T* u = lds + pl.uoff[l];
             const T* f = lds + pl.foff[l];
             pad_load_own<T, NX>(pl.cst[l], on, tid);
-            if constexpr (LEX) {
-                if (threadIdx.x < 64) pad_lex<T, NX>(pl.sten[l], pl.rdiag[l], u, f, false, nu1);
-                __syncthreads();
-            } else {
-                pad_smooth<T, NX>(on, u, f, false, nu1, tid);
-            }
+            if constexpr (!LEX) pad_smooth<T, NX>(on, u, f, false, nu1, tid);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 int x, y;
@@ -1850,13 +1912,9 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_pad(PadLevels<T>
                         [&](int X, int Y) { return ec[(Y + 1) * (NXC + 2) + X + 1]; }, NXC, x, y, pl.p1 != 0);
             }
             __syncthreads();
-            if constexpr (LEX) {
-                if (threadIdx.x < 64) pad_lex<T, NX>(pl.sten[l], pl.rdiag[l], u, f, true, nu2);
-                __syncthreads();
-            } else {
-                pad_smooth<T, NX>(on, u, f, true, nu2, tid);
-            }
+            if constexpr (!LEX) pad_smooth<T, NX>(on, u, f, true, nu2, tid);
         });
+        if constexpr (LEX) lex(l, true, nu2);
     }
     {
         const T* u0 = lds + pl.uoff[0];
@@ -1930,6 +1988,7 @@ struct LevelPtr<double> {
     static const double* cst(const Level& l) { return l.cst64; }
     static const double* stp(const Level& l) { return l.stp64; }
     static const double* sps(const Level& l) { return l.sps64; }
+    static const double* lex(const Level& l) { return l.lex64; }
 };
 template <>
 struct LevelPtr<float> {
@@ -1942,6 +2001,7 @@ struct LevelPtr<float> {
     static const float* cst(const Level& l) { return l.cst32; }
     static const float* stp(const Level& l) { return l.stp32; }
     static const float* sps(const Level& l) { return l.sps32; }
+    static const float* lex(const Level& l) { return l.lex32; }
 };
 
 template <typename T>
@@ -1956,19 +2016,31 @@ void launch_gs(const Tile& tl, dim3 g, hipStream_t st, const T* sten, const T* r
                            width, rb, q, nxc, nyc, first);
 }
 
+// one lexicographic sweep of `width` columns; grids of more rows than a wavefront has lanes (or strides
+// that 32-bit offsets do not hold) walk the fronts with a workgroup per column
+template <typename T>
+void launch_lex(hipStream_t st, Level& lv, T* u, int ldu, const T* f, int ldf, int width, bool reverse, bool first) {
+    const int nx = lv.nx;
+    const T* lex = LevelPtr<T>::lex(lv);
+    if (lex && (size_t)lv.N * (ldu > ldf ? ldu : ldf) * sizeof(T) < 0x80000000ull) {
+        lex += reverse ? lex_elems(nx) : 0;
+        if (first)
+            hipLaunchKernelGGL((k_lex_sweep<T, true>), dim3(width), dim3(kLexThreads), 0, st, lex, u, ldu, f, ldf, nx, reverse);
+        else
+            hipLaunchKernelGGL((k_lex_sweep<T, false>), dim3(width), dim3(kLexThreads), 0, st, lex, u, ldu, f, ldf, nx, reverse);
+    } else {
+        hipLaunchKernelGGL(k_gs_lex<T>, dim3(width), dim3(256), 0, st, LevelPtr<T>::s(lv), LevelPtr<T>::rd(lv), u, ldu, f,
+                           ldf, nx, reverse ? 1 : 0, first ? 1 : 0);
+    }
+}
+
 template <typename T>
 void smooth(sg_ctx* c, int l, T* u, int ldu, const T* f, int ldf, int width, bool reverse, const Tile& tl,
             bool first) {
     Level& lv = c->levels[l];
     const int nx = lv.nx;
     if (c->opt.colour_mode == SG_COLOUR_LEX) {
-        if (nx <= kLexWaveMaxNx)
-            hipLaunchKernelGGL(k_lex_wave<T>, dim3(width), dim3(64), (size_t)(nx + 2) * (nx + 2) * sizeof(T), c->stream,
-                               LevelPtr<T>::s(lv), LevelPtr<T>::rd(lv), u, ldu, f, ldf, nx, reverse ? 1 : 0,
-                               first ? 1 : 0);
-        else
-            hipLaunchKernelGGL(k_gs_lex<T>, dim3(width), dim3(256), 0, c->stream, LevelPtr<T>::s(lv),
-                               LevelPtr<T>::rd(lv), u, ldu, f, ldf, nx, reverse ? 1 : 0, first ? 1 : 0);
+        launch_lex<T>(c->stream, lv, u, ldu, f, ldf, width, reverse, first);
         return;
     }
     const bool rb = c->opt.colour_mode == SG_COLOUR_RB;
@@ -2166,13 +2238,12 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
                 pl.foff[i] = off;
                 off += lv.N;
                 pl.cst[i] = LevelPtr<T>::cst(lv);
-                pl.sten[i] = LevelPtr<T>::s(lv);
-                pl.rdiag[i] = LevelPtr<T>::rd(lv);
+                pl.lex[i] = LevelPtr<T>::lex(lv);
             }
             pl.roff = off;
             off += c->levels[Lc].N;
             if (lex)
-                hipLaunchKernelGGL((k_vcycle_pad<T, true>), dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
+                hipLaunchKernelGGL((k_vcycle_pad<T, true>), dim3(width), dim3((pad_threads<T, true>())), (size_t)off * sizeof(T),
                                    c->stream, pl, (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc),
                                    c->opt.nu1, c->opt.nu2, pc);
             else
@@ -2193,6 +2264,7 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
                 fl.off[i] = off;
                 fl.sten[i] = LevelPtr<T>::s(lv);
                 fl.rdiag[i] = LevelPtr<T>::rd(lv);
+                fl.lex[i] = LevelPtr<T>::lex(lv);
                 off += 2 * lv.N;
             }
             fl.roff = off;
@@ -2202,8 +2274,12 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
                 hipLaunchKernelGGL(k_vcycle_fused4<T>, dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, fl,
                                    (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2, pc);
+            else if (lex)
+                hipLaunchKernelGGL((k_vcycle_fused<T, true>), dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
+                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2,
+                                   c->opt.colour_mode == SG_COLOUR_LEX ? 2 : 1);
             else
-                hipLaunchKernelGGL(k_vcycle_fused<T>, dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
+                hipLaunchKernelGGL((k_vcycle_fused<T, false>), dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
                                    (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2,
                                    c->opt.colour_mode == SG_COLOUR_LEX ? 2 : 1);
         } else {
@@ -2341,8 +2417,12 @@ int launch_level_setup(hipStream_t s, Level& lv) {
     }
     hipLaunchKernelGGL(k_level_setup, dim3((lv.N + 255) / 256), dim3(256), 0, s, lv.sten64, lv.nx, lv.sten32, lv.rdiag64,
                        lv.rdiag32, lv.stp64, lv.stp32, lv.sps64, lv.sps32, lv.cst64, lv.cst32);
+    if (lv.lex64)
+        hipLaunchKernelGGL(k_lex_setup, dim3(2 * lex_chunks(lv.nx) * kLexChunk), dim3(64), 0, s, lv.sten64, lv.nx, lv.lex64,
+                           lv.lex32);
     return hipGetLastError() == hipSuccess ? SG_OK : SG_EHIP;
 }
+size_t lex_setup_elems(int nx) { return nx <= kLexMaxNx ? 2 * lex_elems(nx) : 0; }
 
 int launch_vcycle(sg_ctx* c, const void* f, int ldf, void* u, int ldu, int width, int is_float) {
     int rc = is_float ? vcycle_t<float>(c, (const float*)f, ldf, (float*)u, ldu, width)
@@ -2414,14 +2494,7 @@ int launch_prolong_block(sg_ctx* c, int l, const double* ec, int ldc, double* u,
 }
 
 int launch_lex_sweep(sg_ctx* c, int l, double* u, int ldu, const double* f, int ldf, int width, int reverse) {
-    const Level& lv = c->levels[l];
-    if (lv.nx <= kLexWaveMaxNx)
-        hipLaunchKernelGGL(k_lex_wave<double>, dim3(width), dim3(64), (size_t)(lv.nx + 2) * (lv.nx + 2) * sizeof(double),
-                           c->stream,
-                           lv.sten64, lv.rdiag64, u, ldu, f, ldf, lv.nx, reverse, 0);
-    else
-        hipLaunchKernelGGL(k_gs_lex<double>, dim3(width), dim3(256), 0, c->stream, lv.sten64, lv.rdiag64, u, ldu, f,
-                           ldf, lv.nx, reverse, 0);
+    launch_lex<double>(c->stream, c->levels[l], u, ldu, f, ldf, width, reverse != 0, false);
     return hipGetLastError() == hipSuccess ? SG_OK : SG_EHIP;
 }
 

@@ -22,9 +22,14 @@ namespace {
 
 // out[node, t] = f[node, lo+t] - self (K_0 u_{lo+t})(node)
 //                - sum over the partners beta of alpha = lo+t of G_k(alpha, beta) (K_k u_beta)(node).
-// One thread per (node, output mode), modes fastest.  The stencils of K_k on
-// this level are block k of sten ((m+1) x N x 9); the partners of a mode are
-// packed first in its row of pidx (beta | k << 16), -1 after the last.
+// Four adjacent lanes per (node, output mode), modes fastest: lane g takes the partners g, g + 4, ... (the
+// K_0 term is lane 3's last), so that a lane's few stencils have all their loads in flight at once; the
+// lanes' sums meet by shuffles.  (With one lane an output the partners' dependent loads run one after
+// another: 17 -> 7 us a launch over 1 to 56 modes on 7^2 to 63^2 nodes.)  The stencils of K_k on this level
+// are block k of sten ((m+1) x N x 9); the partners of a mode are packed first in its row of pidx
+// (beta | k << 16), -1 after the last.
+constexpr int kCoupleLanes = 4;
+constexpr int kCoupleTerms = 4;  // terms of a lane: at most 2 m = 16 partners
 __global__ void __launch_bounds__(256) k_split_couple(const double* __restrict__ sten, int N,
                                                       const int* __restrict__ pidx,
                                                       const double* __restrict__ pcoef, int npart,
@@ -32,35 +37,49 @@ __global__ void __launch_bounds__(256) k_split_couple(const double* __restrict__
                                                       const double* __restrict__ f, int ldf,
                                                       double* __restrict__ out, int ldo, int nx, int lo, int width,
                                                       int self) {
-    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (long)N * width) return;
+    const long idx = ((long)blockIdx.x * blockDim.x + threadIdx.x) / kCoupleLanes;
+    const int g = threadIdx.x % kCoupleLanes;
+    if (idx >= (long)N * width) return;  // whole groups of lanes
     const int node = (int)(idx / width), t = (int)(idx - (long)node * width), a = lo + t;
     const int y = node / nx, x = node - y * nx;
+    // the nine nodes around this one, clamped into the grid, and which of them it has
+    int nb[9];
+    bool in[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+        const int xx = x + e % 3 - 1, yy = y + e / 3 - 1;
+        in[e] = xx >= 0 && xx < nx && yy >= 0 && yy < nx;
+        nb[e] = in[e] ? yy * nx + xx : node;
+    }
+    int p[kCoupleTerms];
+    double c[kCoupleTerms];
+#pragma unroll
+    for (int i = 0; i < kCoupleTerms; ++i) {
+        const int q = g + i * kCoupleLanes;
+        p[i] = q < npart ? pidx[a * npart + q] : -1;
+        c[i] = q < npart ? pcoef[a * npart + q] : 0.0;
+    }
     // (K_k u_b)(node)
     auto stencil = [&](int k, int b) -> double {
         const double* s9 = sten + ((size_t)k * N + node) * 9;
-        double v = 0.0;
+        double s[9], w[9], v = 0.0;
 #pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-            const int yy = y + dy;
-            if (yy < 0 || yy >= nx) continue;
-#pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int xx = x + dx;
-                if (xx < 0 || xx >= nx) continue;
-                v = fma(s9[(dy + 1) * 3 + (dx + 1)], u[(size_t)(yy * nx + xx) * ldu + b], v);
-            }
+        for (int e = 0; e < 9; ++e) {
+            s[e] = s9[e];
+            w[e] = u[(size_t)nb[e] * ldu + b];
         }
+#pragma unroll
+        for (int e = 0; e < 9; ++e) v = fma(s[e], in[e] ? w[e] : 0.0, v);
         return v;
     };
-    double acc = f[(size_t)node * ldf + a];
-    if (self) acc -= stencil(0, a);
-    for (int q = 0; q < npart; ++q) {
-        const int e = pidx[a * npart + q];
-        if (e < 0) break;
-        acc -= pcoef[a * npart + q] * stencil(e >> 16, e & 0xFFFF);
-    }
-    out[(size_t)node * ldo + t] = acc;
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < kCoupleTerms; ++i)
+        if (p[i] >= 0) acc = fma(c[i], stencil(p[i] >> 16, p[i] & 0xFFFF), acc);
+    if (self && g == kCoupleLanes - 1) acc += stencil(0, a);
+#pragma unroll
+    for (int o = 1; o < kCoupleLanes; o <<= 1) acc += __shfl_xor(acc, o);
+    if (g == 0) out[(size_t)node * ldo + t] = f[(size_t)node * ldf + a] - acc;
 }
 
 // u = A_hat_c^{-1} f on the coarsest level: one wavefront per row of the
@@ -89,7 +108,7 @@ int launch_split_couple(sg_ctx* c, int l, const double* u, int ldu, const double
                         int lo, int width, int self) {
     const SplitDev& sp = c->split;
     const Level& lv = c->levels[l];
-    const long total = (long)lv.N * width;
+    const long total = (long)lv.N * width * kCoupleLanes;
     if (total == 0) return SG_OK;
     hipLaunchKernelGGL(k_split_couple, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream, sp.sten[l],
                        lv.N, sp.pidx, sp.pcoef, sp.npart, u, ldu, f, ldf, out, ldo, lv.nx, lo, width, self);

@@ -100,3 +100,21 @@ def test_preconditioners_at_odd_level_widths():
             assert rel_max(to_host(g.precond(to_dev(r), kind=kind)), ref) < 1e-11
             assert rel_max(to_host(g.precond(to_dev(r), kind=kind, prec=sgbt.SG_MIXED)), ref) < 5e-5
         g.close()
+
+
+@pytest.mark.parametrize("n,coarsest", [(64, 4), (48, 3), (60, 15), (128, 8)])
+@pytest.mark.parametrize("width,prec", [(1, "f64"), (5, "f64"), (3, "f32")])
+def test_lexicographic_sweeps(n, coarsest, width, prec):
+    """The lexicographic cycle by fronts: 63 rows (every lane but one), 47 and 23 (a hierarchy that is not
+    2^k - 1), 59 and 29, and 127 (more rows than lanes: the barrier form above the fronts)."""
+    import sg_inputs
+    import paper_1304_1755_amd as sgbt
+    from oracle import mg, system
+    note(f"lex n={n} coarsest={coarsest} width={width} {prec}")
+    o = system.build_problem(n, 1, 1, 0.3, 0.5)
+    H = mg.Hierarchy(o.K[0], n, coarsest=coarsest, colour_mode="lex")
+    g = sgbt.Problem(n, 2, 2, 0.3, coarsest=coarsest, colour="lex")
+    f = to_dev(sg_inputs.uniform_block(g.N, width, seed=n), torch.float32 if prec == "f32" else torch.float64)
+    u = g.vcycle(f, prec=sgbt.SG_F32 if prec == "f32" else sgbt.SG_F64)
+    assert rel_max(to_host(u), H.vcycle(to_host(f))) < (2e-5 if prec == "f32" else 1e-11)
+    g.close()
