@@ -63,6 +63,12 @@ constexpr int kApplyRows = 2;        // grid rows per workgroup
 constexpr int kMinApplyWaves = 16384;
 constexpr int min_apply_waves(int ns) { return ns >= 4 ? kMinApplyWaves : 4 * kMinApplyWaves; }
 
+// below this many wavefronts (two a SIMD) a walk of 8 columns is the launch's whole time: shorter ones
+// finish sooner although they load more halo columns (us a launch with 8 and with fewer: 31^2 P = 6
+// 6.9 and 3.8, P = 210 10.7 and 5.0; 63^2 P = 210 11.5 and 9.0; 127^2 P = 35 9.7 and 7.6; with 4096
+// 127^2 P = 6 takes 6.7 instead of 6.3)
+constexpr int kShortApplyWaves = 2048;
+
 template <typename F, int... J>
 __device__ __forceinline__ void unroll_steps(F&& f, std::integer_sequence<int, J...>) {
     (f(std::integral_constant<int, J>{}), ...);
@@ -297,6 +303,8 @@ hipError_t launch_t(hipStream_t st, const Plan& pl, const void* U, int ldu, cons
     // enough wavefronts to cover the chip (each segment's walk is sequential)
     int seg = 32;
     while (seg > 8 && (long)((nx + RW - 1) / RW) * ((nx + seg - 1) / seg) * NS < min_apply_waves(NS)) seg >>= 1;
+    // launches below kShortApplyWaves even so: down to 2
+    while (seg > 2 && (long)((nx + RW - 1) / RW) * ((nx + seg - 1) / seg) * NS < kShortApplyWaves) seg >>= 1;
     const int nseg = (nx + seg - 1) / seg;
     const int blocks = (nx + RW - 1) / RW * nseg;
     if (R)

@@ -726,12 +726,12 @@ hipError_t up_t(hipStream_t st, const T* sps, const T* f, int ldf, const T* ui, 
 
 }  // namespace
 
-// 16 bytes of modes a lane and load; narrow float blocks take 8, which fills less up and leaves more
-// wavefronts (a cycle at 511^2, float, with 4 and with 2 modes a lane: W = 126 444 and 502 us, W = 56 237
-// and 248, B_T at P = 210 1442 and 1575)
+// 16 bytes of modes a lane and load; narrower float blocks take 8, which fills less up and leaves more
+// wavefronts (a cycle at 511^2, float, with 4 and with 2 modes a lane: W = 126 444 and 502 us, W = 56 233
+// and 244, W = 35 214 and 208, W = 21 175 and 148)
 int stream_modes(int is_float, int width) {
     if (width < 2) return 1;
-    return is_float && width >= 16 ? 4 : 2;
+    return is_float && width >= 40 ? 4 : 2;
 }
 
 hipError_t stream_down(hipStream_t st, const float* sps, const float* f, int ldf, float* uo, float* fc, int nx, int width,

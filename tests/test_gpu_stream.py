@@ -34,7 +34,7 @@ def _check(n, coarsest, width, prec, nu1, nu2, disc):
     import paper_1304_1755_amd as sgbt
     note(f"stream n={n} coarsest={coarsest} width={width} prec={prec} nu={nu1},{nu2} {disc}")
     H = _oracle(n, coarsest, nu1, nu2, disc)
-    g = sgbt.Problem(n, 4, 3, 0.2 if disc == "p1" else 0.3, corr_len=1.0 if disc == "p1" else 0.5, coarsest=coarsest,
+    g = sgbt.Problem(n, 4, 4 if width > 35 else 3, 0.2 if disc == "p1" else 0.3, corr_len=1.0 if disc == "p1" else 0.5, coarsest=coarsest,
                      nu1=nu1, nu2=nu2, disc=disc)
     f = sg_inputs.uniform_block(g.N, width, seed=n + width)
     dt = torch.float32 if prec == "f32" else torch.float64
@@ -51,8 +51,8 @@ def _check(n, coarsest, width, prec, nu1, nu2, disc):
     g.close()
 
 
-@pytest.mark.parametrize("width,prec", [(1, "f32"), (3, "f32"), (7, "f32"), (16, "f32"), (21, "f32"), (1, "f64"),
-                                        (3, "f64"), (8, "f64"), (35, "f64")])
+@pytest.mark.parametrize("width,prec", [(1, "f32"), (3, "f32"), (7, "f32"), (21, "f32"), (34, "f32"), (1, "f64"),
+                                        (3, "f64"), (8, "f64"), (35, "f64"), (40, "f32"), (47, "f32")])
 @pytest.mark.parametrize("n,coarsest", GRIDS)
 def test_stream_cycle_matches_oracle(n, coarsest, width, prec):
     _check(n, coarsest, width, prec, 2, 2, "q1")
