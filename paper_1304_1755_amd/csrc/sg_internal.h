@@ -250,9 +250,9 @@ int launch_apply_p1(sg_ctx* c, const Plan& pl, const void* U, int in_float, cons
 // from ui + P ec; uo must not overlap ui.
 int stream_modes(int is_float, int width);
 hipError_t stream_down(hipStream_t st, const float* sps, const float* f, int ldf, float* uo, float* fc, int nx, int width,
-                       int nu);
+                       int nu, bool p1);
 hipError_t stream_down(hipStream_t st, const double* sps, const double* f, int ldf, double* uo, double* fc, int nx,
-                       int width, int nu);
+                       int width, int nu, bool p1);
 hipError_t stream_up(hipStream_t st, const float* sps, const float* f, int ldf, const float* ui, const float* ec, float* uo,
                      int ldo, int nx, int width, int nu, bool p1);
 hipError_t stream_up(hipStream_t st, const double* sps, const double* f, int ldf, const double* ui, const double* ec,

@@ -2294,7 +2294,7 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
     if (stream) {
         for (int l = 0; l < Ltop; ++l)
             if (stream_down(c->stream, LevelPtr<T>::sps(c->levels[l]), fptr(l), l == 0 ? ldf0 : 0, uptr(l),
-                            LevelPtr<T>::f(c->levels[l + 1]), c->levels[l].nx, width, c->opt.nu1) != hipSuccess)
+                            LevelPtr<T>::f(c->levels[l + 1]), c->levels[l].nx, width, c->opt.nu1, p1) != hipSuccess)
                 return SG_EHIP;
         if (int rc = coarse_part()) return rc;
         for (int l = Ltop - 1; l >= 0; --l)

@@ -306,31 +306,47 @@ struct Stencils {
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
-__device__ __forceinline__ float sub_mul(float a, float c, float v) { return fmaf(-c, v, a); }
-__device__ __forceinline__ double sub_mul(double a, double c, double v) { return fma(-c, v, a); }
 
-// f minus the row below, and the row above, at the even / odd column: two sums, which keeps the chains
-// short and the rounding as small as that of k_gs_rows
-template <typename T, int M>
-__device__ __forceinline__ T rest_e(const PairStencil<T>& st, T f, const Pair<T, M>& d, const Pair<T, M>& u, int m) {
-    const T a = fma_t(st.e[0], from_left(d.o[m]), fma_t(st.e[2], d.o[m], st.e[1] * d.e[m]));
-    const T b = fma_t(st.e[6], from_left(u.o[m]), fma_t(st.e[8], u.o[m], st.e[7] * u.e[m]));
-    return (f - a) - b;
+// K u at the even / odd column: the share of the row below or above (its coefficients from st.e[R] or
+// st.o[R] on), and of the left and right neighbours (the even node's left one is the odd node of the lane
+// before).  Three short sums keep the chains short and the rounding as small as that of k_gs_rows.
+template <int R, typename T, int M>
+__device__ __forceinline__ T row_e(const PairStencil<T>& st, const Pair<T, M>& v, int m) {
+    return fma_t(st.e[R], from_left(v.o[m]), fma_t(st.e[R + 2], v.o[m], st.e[R + 1] * v.e[m]));
 }
-template <typename T, int M>
-__device__ __forceinline__ T rest_o(const PairStencil<T>& st, T f, const Pair<T, M>& d, const Pair<T, M>& u, int m) {
-    const T a = fma_t(st.o[2], from_right(d.e[m]), fma_t(st.o[0], d.e[m], st.o[1] * d.o[m]));
-    const T b = fma_t(st.o[8], from_right(u.e[m]), fma_t(st.o[6], u.e[m], st.o[7] * u.o[m]));
-    return (f - a) - b;
-}
-// the left and right neighbours' share (the even node's left one is the odd node of the lane before)
-template <typename T>
-__device__ __forceinline__ T side_e(const PairStencil<T>& st, T a, T o) {
-    return a - fma_t(st.e[3], from_left(o), st.e[5] * o);
+template <int R, typename T, int M>
+__device__ __forceinline__ T row_o(const PairStencil<T>& st, const Pair<T, M>& v, int m) {
+    return fma_t(st.o[R + 2], from_right(v.e[m]), fma_t(st.o[R], v.e[m], st.o[R + 1] * v.o[m]));
 }
 template <typename T>
-__device__ __forceinline__ T side_o(const PairStencil<T>& st, T a, T e) {
-    return a - fma_t(st.o[5], from_right(e), st.o[3] * e);
+__device__ __forceinline__ T side_e(const PairStencil<T>& st, T o) {
+    return fma_t(st.e[3], from_left(o), st.e[5] * o);
+}
+template <typename T>
+__device__ __forceinline__ T side_o(const PairStencil<T>& st, T e) {
+    return fma_t(st.o[5], from_right(e), st.o[3] * e);
+}
+// f minus the neighbours
+template <typename T, int M>
+__device__ __forceinline__ T rest_e(const PairStencil<T>& st, T f, const Pair<T, M>& d, T o, const Pair<T, M>& u, int m) {
+    return ((f - row_e<0>(st, d, m)) - row_e<6>(st, u, m)) - side_e(st, o);
+}
+template <typename T, int M>
+__device__ __forceinline__ T rest_o(const PairStencil<T>& st, T f, const Pair<T, M>& d, T e, const Pair<T, M>& u, int m) {
+    return ((f - row_o<0>(st, d, m)) - row_o<6>(st, u, m)) - side_o(st, e);
+}
+// f - K u at a node of the row w.  The node's own share cancels the neighbours', so it is taken in with the
+// row's, before the sum has grown: the sums stay within half of it, and their rounding with them (a float
+// cycle of the P1 triangulation is 12 % further from the exact one with the own share last).
+template <typename T, int M>
+__device__ __forceinline__ T resid_e(const PairStencil<T>& st, T f, const Pair<T, M>& d, const Pair<T, M>& w,
+                                     const Pair<T, M>& u, int m) {
+    return ((f - row_e<0>(st, d, m)) - fma_t(st.e[4], w.e[m], side_e(st, w.o[m]))) - row_e<6>(st, u, m);
+}
+template <typename T, int M>
+__device__ __forceinline__ T resid_o(const PairStencil<T>& st, T f, const Pair<T, M>& d, const Pair<T, M>& w,
+                                     const Pair<T, M>& u, int m) {
+    return ((f - row_o<0>(st, d, m)) - fma_t(st.o[4], w.o[m], side_o(st, w.e[m]))) - row_o<6>(st, u, m);
 }
 
 // makes the values of a row unrecognisable: the shifts of one phase would otherwise be kept for the
@@ -349,11 +365,11 @@ __device__ __forceinline__ void relax_row(const PairStencil<T>& st, const Pair<T
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         if constexpr (FWD) {
-            n.o[m] = side_o(st, rest_o(st, f.o[m], d, u, m), w.e[m]) * st.o[9];
-            n.e[m] = side_e(st, rest_e(st, f.e[m], d, u, m), n.o[m]) * st.e[9];
+            n.o[m] = rest_o(st, f.o[m], d, w.e[m], u, m) * st.o[9];
+            n.e[m] = rest_e(st, f.e[m], d, n.o[m], u, m) * st.e[9];
         } else {
-            n.e[m] = side_e(st, rest_e(st, f.e[m], d, u, m), w.o[m]) * st.e[9];
-            n.o[m] = side_o(st, rest_o(st, f.o[m], d, u, m), n.e[m]) * st.o[9];
+            n.e[m] = rest_e(st, f.e[m], d, w.o[m], u, m) * st.e[9];
+            n.o[m] = rest_o(st, f.o[m], d, n.e[m], u, m) * st.o[9];
         }
     }
 }
@@ -405,15 +421,16 @@ __device__ __forceinline__ void fence_schedule() { __builtin_amdgcn_sched_barrie
 template <typename T, int M>
 constexpr int stream_waves() { return M * sizeof(T) == 4 ? 3 : 2; }
 
-// u = NU forward sweeps from zero on K u = f; fc = P^T (f - K u).  After a
-// forward sweep the residual of the last colour (even row, even column) is
-// zero, so it is not formed and the bilinear and the P1 restriction, which
-// differ in the weights of that colour only, are the same sum.
+// u = NU forward sweeps from zero on K u = f; fc = P^T (f - K u) (P1T: the
+// transfer of the triangulation).  The residual of the last colour (even row,
+// even column) is no more than what the rounding of its relaxation left, but the
+// coarse grid corrects it: without it a float cycle is 2 to 10 % further from
+// the exact one.
 //
 // The rows in flight sit in rings indexed by the step (values two steps, right-
 // hand sides four, one of them being loaded), and the walk is unrolled by four so
 // that every index is a constant and no register is moved.
-template <typename T, int M, int NU, bool SH>
+template <typename T, int M, int NU, bool P1T, bool SH>
 __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(const T* __restrict__ sps, const T* __restrict__ f, int ldf,
                                                      T* __restrict__ uo, T* __restrict__ fc, int nx, int width, int nch, int ns,
                                                      int seg, int nseg) {
@@ -425,11 +442,11 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
     const bool ownc = s.own && X < nxc;
     // values by phase (a: odd rows, b: even rows; 1, 2: sweep) and right-hand sides of the rows in flight
     Pair<T, M> a1[2], b1[2], a2[2], b2[2], fo[4], fe[4];
-    T rn[2][M];  // residual of an even row, odd column
+    T rl[M];  // share of the even row below in the restriction
     clear(a1[1]); clear(b1[1]); clear(a2[1]); clear(b2[1]);
     clear(fo[3]); clear(fo[2]); clear(fe[3]);
 #pragma unroll
-    for (int m = 0; m < M; ++m) rn[1][m] = T(0);
+    for (int m = 0; m < M; ++m) rl[m] = T(0);
     const int k0 = s.Y0 - 2, k1 = s.Y1 + 1;
     Stencils<T, SH> sten;
     sten.begin(sps, nx, s, ring);
@@ -456,7 +473,7 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             a1[c].o[m] = fo[J].o[m] * s0.o[9];
-            a1[c].e[m] = side_e(s0, fo[J].e[m], a1[c].o[m]) * s0.e[9];
+            a1[c].e[m] = (fo[J].e[m] - side_e(s0, a1[c].o[m])) * s0.e[9];
         }
         if constexpr (!SH && NU == 2) sten.get(2 * k - 1, (2 * J + 7) & 7, s0);
         fence_schedule();
@@ -464,8 +481,8 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
         // sweep 1, row 2k: the row itself is still zero
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            b1[c].o[m] = rest_o(s1, fe[J].o[m], a1[p], a1[c], m) * s1.o[9];
-            b1[c].e[m] = side_e(s1, rest_e(s1, fe[J].e[m], a1[p], a1[c], m), b1[c].o[m]) * s1.e[9];
+            b1[c].o[m] = ((fe[J].o[m] - row_o<0>(s1, a1[p], m)) - row_o<6>(s1, a1[c], m)) * s1.o[9];
+            b1[c].e[m] = rest_e(s1, fe[J].e[m], a1[p], b1[c].o[m], a1[c], m) * s1.e[9];
         }
         if constexpr (!SH) sten.get(2 * k - 2, (2 * J + 6) & 7, s1);
         forget(a1[p]);
@@ -480,10 +497,15 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
         if constexpr (SH) sten.get(2 * k - 2, (2 * J + 6) & 7, s1);
         if constexpr (NU == 2) relax_row<true, T, M>(s1, fe[j1], b1[p], a2[p], a2[c], b2[c]);
         else b2[c] = b1[p];
-        // residual at row 2k-2 (odd column; the even one is zero)
+        // residual at row 2k-2 and the row's share in the coarse rows above (ru) and below it: the odd
+        // column's with both corners' means, or (P1T) the north-east or the south-west corner
+        T ru[M], rd[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m)
-            rn[c][m] = sub_mul(side_o(s1, rest_o(s1, fe[j1].o[m], a2[p], a2[c], m), b2[c].e[m]), s1.o[4], b2[c].o[m]);
+        for (int m = 0; m < M; ++m) {
+            const T o = resid_o(s1, fe[j1].o[m], a2[p], b2[c], a2[c], m), e = resid_e(s1, fe[j1].e[m], a2[p], b2[c], a2[c], m);
+            rd[m] = o + (P1T ? from_right(e) : T(0.5) * (e + from_right(e)));
+            ru[m] = P1T ? o + e : rd[m];
+        }
         const int y = 2 * k - 2;
         if (y >= 2 * s.Y0 && (y < 2 * s.Y1 || s.last)) {
             store_row<T, M>(wu, y, s, b2[c]);
@@ -498,13 +520,15 @@ __global__ void __launch_bounds__(256, (stream_waves<T, M>())) k_stream_down(con
             T v[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                T re = sub_mul(side_e(s0, rest_e(s0, fo[j2].e[m], b2[p], b2[c], m), a2[p].o[m]), s0.e[4], a2[p].e[m]);
+                T re = resid_e(s0, fo[j2].e[m], b2[p], a2[p], b2[c], m);
                 re = s.ine ? re : T(0);
-                const T ro = sub_mul(side_o(s0, rest_o(s0, fo[j2].o[m], b2[p], b2[c], m), a2[p].e[m]), s0.o[4], a2[p].o[m]);
-                v[m] = ro + T(0.5) * ((rn[p][m] + rn[c][m]) + (re + from_right(re)));
+                const T ro = resid_o(s0, fo[j2].o[m], b2[p], a2[p], b2[c], m);
+                v[m] = ro + T(0.5) * ((rl[m] + rd[m]) + (re + from_right(re)));
             }
             if (ownc) store_modes<T, M>(wc.b, wc.e, (unsigned)(k - 2 - wc.y0) * wc.pitch, v, 0);
         }
+#pragma unroll
+        for (int m = 0; m < M; ++m) rl[m] = ru[m];
         forget(a1[c]);
         forget(b1[c]);
         forget(a2[c]);
@@ -666,15 +690,15 @@ StreamShape stream_shape(int nx, int nch) {
     return h;
 }
 
-template <typename T, int M, int NU>
+template <typename T, int M, int NU, bool P1T>
 hipError_t down_m(hipStream_t st, const T* sps, const T* f, int ldf, T* uo, T* fc, int nx, int width) {
     const int nch = (width + M - 1) / M;
     const StreamShape h = stream_shape(nx, nch);
     if (h.shared)
-        hipLaunchKernelGGL((k_stream_down<T, M, NU, true>), dim3((nch + kShWaves - 1) / kShWaves * h.ns * h.nseg), dim3(256),
+        hipLaunchKernelGGL((k_stream_down<T, M, NU, P1T, true>), dim3((nch + kShWaves - 1) / kShWaves * h.ns * h.nseg), dim3(256),
                            0, st, sps, f, ldf, uo, fc, nx, width, nch, h.ns, h.seg, h.nseg);
     else
-        hipLaunchKernelGGL((k_stream_down<T, M, NU, false>), dim3((nch * h.ns * h.nseg + 3) / 4), dim3(256), 0, st, sps, f,
+        hipLaunchKernelGGL((k_stream_down<T, M, NU, P1T, false>), dim3((nch * h.ns * h.nseg + 3) / 4), dim3(256), 0, st, sps, f,
                            ldf, uo, fc, nx, width, nch, h.ns, h.seg, h.nseg);
     return hipGetLastError();
 }
@@ -709,9 +733,11 @@ hipError_t with_shape(int width, int nu, F go) {
 }
 
 template <typename T>
-hipError_t down_t(hipStream_t st, const T* sps, const T* f, int ldf, T* uo, T* fc, int nx, int width, int nu) {
+hipError_t down_t(hipStream_t st, const T* sps, const T* f, int ldf, T* uo, T* fc, int nx, int width, int nu, bool p1) {
     return with_shape<T>(width, nu, [&](auto m, auto n) {
-        return down_m<T, decltype(m)::value, decltype(n)::value>(st, sps, f, ldf, uo, fc, nx, width);
+        constexpr int M = decltype(m)::value, NU = decltype(n)::value;
+        return p1 ? down_m<T, M, NU, true>(st, sps, f, ldf, uo, fc, nx, width)
+                  : down_m<T, M, NU, false>(st, sps, f, ldf, uo, fc, nx, width);
     });
 }
 template <typename T>
@@ -735,12 +761,12 @@ int stream_modes(int is_float, int width) {
 }
 
 hipError_t stream_down(hipStream_t st, const float* sps, const float* f, int ldf, float* uo, float* fc, int nx, int width,
-                       int nu) {
-    return down_t<float>(st, sps, f, ldf, uo, fc, nx, width, nu);
+                       int nu, bool p1) {
+    return down_t<float>(st, sps, f, ldf, uo, fc, nx, width, nu, p1);
 }
-hipError_t stream_down(hipStream_t st, const double* sps, const double* f, int ldf, double* uo, double* fc, int nx,
-                       int width, int nu) {
-    return down_t<double>(st, sps, f, ldf, uo, fc, nx, width, nu);
+hipError_t stream_down(hipStream_t st, const double* sps, const double* f, int ldf, double* uo, double* fc, int nx, int width,
+                       int nu, bool p1) {
+    return down_t<double>(st, sps, f, ldf, uo, fc, nx, width, nu, p1);
 }
 hipError_t stream_up(hipStream_t st, const float* sps, const float* f, int ldf, const float* ui, const float* ec, float* uo,
                      int ldo, int nx, int width, int nu, bool p1) {
