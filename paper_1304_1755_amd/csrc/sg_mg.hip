@@ -1243,17 +1243,18 @@ __device__ __forceinline__ void lex_sweep(const T* __restrict__ lex, int nx, T* 
                 __builtin_amdgcn_sched_barrier(0);
                 const V2* k = w[j];
                 const T ne = k[4].y;
-                T p = k[0].x * k[5].x;
-                p = lex_fma(-k[0].y, k[5].y, p);
+                // the old values' share comes last: the sum is then nowhere larger than it has to be, and
+                // its rounding with it
                 T q = k[1].x * n;
                 q = lex_fma(k[1].y, ne, q);
                 q = lex_fma(k[2].x, nw, q);
+                q = lex_fma(k[0].y, k[5].y, q);
+                T p = k[0].x * k[5].x;
                 p = lex_fma(-k[2].y, s, p);
                 p = lex_fma(-k[3].x, sw, p);
-                p -= q;
                 p = lex_fma(-k[3].y, v, p);
                 const T se = lane_below(v);
-                v = lex_fma(-k[4].x, se, p);
+                v = lex_fma(-k[4].x, se, p) - q;
                 put(c * kLexChunk + j, v);
                 sw = s;
                 s = se;
