@@ -1130,12 +1130,16 @@ __device__ __forceinline__ void lex_front(int d, int nx, int& ylo, int& yhi) {
 // lane relaxes the node (d - 2t, t) of its row.  Of the node's four new
 // neighbours the west one is the lane's own last value, and the three below it
 // are the last three values of lane t - 1, one DPP wave shift a front.  So a front
-// depends on the one before through one shift and two multiply-adds.  What the
+// depends on the one before through one shift, two multiply-adds and a subtraction.  What the
 // sweep does not change -- the coefficients (divided by the diagonal, front by
 // front, zero where a lane has no node or a neighbour lies outside the grid), the
 // right-hand side, the old east and north-east values -- seven more wavefronts of
 // the workgroup bring into LDS, a front each at a time, and hold the next
 // kLexAhead fronts each on their way (a front takes less time than a load).
+// Two are enough, as the ring itself is two chunks ahead; with six the inlined
+// sweeps of the LDS cycle spilled (187 registers in double), and a short sweep
+// waited for loads past its end: a cycle at 15^2, P = 210, double 68 -> 86 us with
+// six against the former sweeps and 63 with two; at 63^2 438, 303 and 268.
 //
 // What bounds it: 3 nx - 2 dependent fronts, about 0.18 us each; the chain itself
 // (a shift and two multiply-adds) would allow a third of that.  A 63^2 sweep of 126
@@ -1145,7 +1149,7 @@ __device__ __forceinline__ void lex_front(int d, int nx, int& ylo, int& yhi) {
 // coupling of k_split_couple.
 constexpr int kLexMaxNx = 63;  // at most 64 rows, one per lane
 constexpr int kLexChunk = 7;   // fronts in LDS at a time, one per loading wavefront
-constexpr int kLexAhead = 6;   // chunks on their way
+constexpr int kLexAhead = 2;   // chunks on their way
 constexpr int kLexThreads = 64 * (kLexChunk + 1);
 constexpr int kLexPieces = 5;  // pairs of coefficients: rd E | N NE | NW S | SW W | SE 0
 constexpr int kLexRing = 3 * kLexChunk * (kLexPieces + 1) * 128;  // elements of the LDS ring: the chunk swept, the next, the one being written
