@@ -29,7 +29,8 @@ namespace {
 // are block k of sten ((m+1) x N x 9); the partners of a mode are packed first in its row of pidx
 // (beta | k << 16), -1 after the last.
 constexpr int kCoupleLanes = 4;
-constexpr int kCoupleTerms = 4;  // terms of a lane: at most 2 m = 16 partners
+constexpr int kCoupleTerms = 4;  // terms of a lane
+static_assert(kCoupleLanes * kCoupleTerms >= 2 * kMaxM, "a mode has up to 2 m partners: a term would be dropped");
 __global__ void __launch_bounds__(256) k_split_couple(const double* __restrict__ sten, int N,
                                                       const int* __restrict__ pidx,
                                                       const double* __restrict__ pcoef, int npart,
