@@ -118,3 +118,9 @@ def test_lexicographic_sweeps(n, coarsest, width, prec):
     u = g.vcycle(f, prec=sgbt.SG_F32 if prec == "f32" else sgbt.SG_F64)
     assert rel_max(to_host(u), H.vcycle(to_host(f))) < (2e-5 if prec == "f32" else 1e-11)
     g.close()
+
+
+def test_longest_segments():
+    """511 nodes a side and 53 (float) or 105 (double) panels: segments of thirty-two coarse rows."""
+    from test_gpu_cycle_forms import _check as check_strided
+    check_strided(512, 8, (210,), 2, 2, "q1")
