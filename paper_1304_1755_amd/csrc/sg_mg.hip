@@ -1451,6 +1451,7 @@ __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const d
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
     T* r = lds + fl.roff;
+    SG_POISON_LDS(ring, LEX ? kLexRing : 1);
     SG_POISON_LDS(lds, fl.roff + fl.nx[0] * fl.nx[0]);
     const int col = blockIdx.x;
     const int L = fl.nlev - 1;
