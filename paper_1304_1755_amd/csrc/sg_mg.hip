@@ -44,6 +44,7 @@
 //     post-smoothing sweep writes the caller's (possibly strided) output.
 
 #include "sg_internal.h"
+#include "sg_wave.h"
 
 namespace sg {
 
@@ -1157,24 +1158,6 @@ constexpr int kLexRing = 3 * kLexChunk * (kLexPieces + 1) * 128;  // elements of
 __host__ __device__ constexpr int lex_chunks(int nx) { return (3 * nx - 2 + kLexChunk - 1) / kLexChunk; }
 __host__ __device__ constexpr size_t lex_elems(int nx) { return (size_t)lex_chunks(nx) * kLexChunk * kLexPieces * 128; }
 
-__device__ __forceinline__ float lane_below(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double lane_below(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lex_fma(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double lex_fma(double a, double b, double c) { return fma(a, b, c); }
-
-// LDS accesses done and every wavefront of the workgroup here (global loads stay in flight)
-__device__ __forceinline__ void lds_meet() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __asm__ __volatile__("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    __asm__ __volatile__("" ::: "memory");
-}
-
 // One sweep, called by all wavefronts of a workgroup of at least kLexThreads; the first one sweeps, the next
 // seven load.  get_f(d), get_e(d, x, y): the calling lane's right-hand side at front d, and its old value
 // x columns east and y rows north of the node of front d, both zero where there is none; put(d, v): the
@@ -1250,15 +1233,15 @@ __device__ __forceinline__ void lex_sweep(const T* __restrict__ lex, int nx, T* 
                 // the old values' share comes last: the sum is then nowhere larger than it has to be, and
                 // its rounding with it
                 T q = k[1].x * n;
-                q = lex_fma(k[1].y, ne, q);
-                q = lex_fma(k[2].x, nw, q);
-                q = lex_fma(k[0].y, k[5].y, q);
+                q = fma_t(k[1].y, ne, q);
+                q = fma_t(k[2].x, nw, q);
+                q = fma_t(k[0].y, k[5].y, q);
                 T p = k[0].x * k[5].x;
-                p = lex_fma(-k[2].y, s, p);
-                p = lex_fma(-k[3].x, sw, p);
-                p = lex_fma(-k[3].y, v, p);
-                const T se = lane_below(v);
-                v = lex_fma(-k[4].x, se, p) - q;
+                p = fma_t(-k[2].y, s, p);
+                p = fma_t(-k[3].x, sw, p);
+                p = fma_t(-k[3].y, v, p);
+                const T se = from_left(v);
+                v = fma_t(-k[4].x, se, p) - q;
                 put(c * kLexChunk + j, v);
                 sw = s;
                 s = se;
@@ -1363,56 +1346,33 @@ __global__ void __launch_bounds__(64) k_lex_setup(const double* __restrict__ ste
     }
 }
 
-// mode 0: four colours; 1: red/black from start-of-colour values; 2: lexicographic
+// nu sweeps of a grid in LDS: lexicographic (LEX), or red/black from start-of-colour values
 template <typename T, bool LEX>
 __device__ void lds_smooth(const T* __restrict__ st, const T* __restrict__ rdiag, const T* __restrict__ lex, T* u,
-                           const T* f, T* stage, int nx, int mode, bool reverse, int nu, T* ring) {
+                           const T* f, T* stage, int nx, bool reverse, int nu, T* ring) {
     if constexpr (LEX) {
         // the first wavefront sweeps (every fused grid has at most 63 rows)
         lds_lex<T>(lex + (reverse ? lex_elems(nx) : 0), ring, u, nx, f, nx, reverse, nu);
         __syncthreads();
         return;
     }
-    const bool rb = mode == 1;
-    const int ncol = rb ? 2 : 4;
+    const int nxc = (nx + 1) / 2;
     for (int sweep = 0; sweep < nu; ++sweep)
-        for (int qi = 0; qi < ncol; ++qi) {
-            const int q = reverse ? ncol - 1 - qi : qi;
-            int nxc, nyc;
-            if (rb) { nxc = (nx + 1) / 2; nyc = nx; }
-            else { nxc = (nx - (((q & 1) ^ 1)) + 1) / 2; nyc = (nx - (((q >> 1) ^ 1)) + 1) / 2; }
-            for (int t = threadIdx.x; t < nxc * nyc; t += blockDim.x) {
-                const int j = t / nxc, i = t - j * nxc;
-                int x, y;
-                if (rb) { y = j; x = ((q + y) & 1) + 2 * i; if (x >= nx) continue; }
-                else { x = ((q & 1) ^ 1) + 2 * i; y = ((q >> 1) ^ 1) + 2 * j; }
+        for (int qi = 0; qi < 2; ++qi) {
+            const int q = reverse ? 1 - qi : qi;
+            for (int t = threadIdx.x; t < nxc * nx; t += blockDim.x) {
+                const int y = t / nxc, i = t - y * nxc, x = ((q + y) & 1) + 2 * i;
+                if (x >= nx) continue;
                 const int node = y * nx + x;
-                const T* s9 = st + (size_t)node * 9;
-                T acc = f[node];
-#pragma unroll
-                for (int dy = -1; dy <= 1; ++dy) {
-                    const int yy = y + dy;
-                    if (yy < 0 || yy >= nx) continue;
-#pragma unroll
-                    for (int dx = -1; dx <= 1; ++dx) {
-                        if (dx == 0 && dy == 0) continue;
-                        const int xx = x + dx;
-                        if (xx < 0 || xx >= nx) continue;
-                        acc -= s9[(dy + 1) * 3 + (dx + 1)] * u[yy * nx + xx];
-                    }
-                }
-                const T val = acc * rdiag[node];
-                if (rb) stage[node] = val; else u[node] = val;
+                stage[node] = relax_node<T>(st + (size_t)node * 9, rdiag[node], f[node], x, y, nx, [&](int n) { return u[n]; });
             }
             __syncthreads();
-            if (rb) {
-                for (int t = threadIdx.x; t < nxc * nyc; t += blockDim.x) {
-                    const int y = t / nxc, i = t - y * nxc;
-                    const int x = ((q + y) & 1) + 2 * i;
-                    if (x < nx) u[y * nx + x] = stage[y * nx + x];
-                }
-                __syncthreads();
+            for (int t = threadIdx.x; t < nxc * nx; t += blockDim.x) {
+                const int y = t / nxc, i = t - y * nxc;
+                const int x = ((q + y) & 1) + 2 * i;
+                if (x < nx) u[y * nx + x] = stage[y * nx + x];
             }
+            __syncthreads();
         }
 }
 
@@ -1446,7 +1406,7 @@ __global__ void __launch_bounds__(256) k_gs_lex(const T* __restrict__ sten, cons
 template <typename T, bool LEX>
 __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const double* __restrict__ kinv,
                                                       const T* __restrict__ fin, int ldf, T* __restrict__ uout,
-                                                      int ldu, int nu1, int nu2, int mode) {
+                                                      int ldu, int nu1, int nu2) {
     __shared__ __attribute__((aligned(16))) T ring[LEX ? kLexRing : 1];
     extern __shared__ char smem_raw[];
     T* lds = (T*)smem_raw;
@@ -1467,7 +1427,7 @@ __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const d
         T* f = u + N;
         for (int i = threadIdx.x; i < N; i += blockDim.x) u[i] = T(0);
         __syncthreads();
-        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, mode, false, nu1, ring);
+        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, false, nu1, ring);
         // residual r = f - K u
         for (int node = threadIdx.x; node < N; node += blockDim.x) {
             const int y = node / nx, x = node - y * nx;
@@ -1519,7 +1479,7 @@ __global__ void __launch_bounds__(512) k_vcycle_fused(FusedLevels<T> fl, const d
             u[node] += prolong_value<T>([&](int X, int Y) { return ec[Y * nxc + X]; }, nxc, x, y, fl.p1 != 0);
         }
         __syncthreads();
-        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, mode, true, nu2, ring);
+        lds_smooth<T, LEX>(fl.sten[l], fl.rdiag[l], fl.lex[l], u, f, r, nx, true, nu2, ring);
     }
     {
         const int N0 = fl.nx[0] * fl.nx[0];
@@ -2282,12 +2242,10 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
                                    (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2, pc);
             else if (lex)
                 hipLaunchKernelGGL((k_vcycle_fused<T, true>), dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
-                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2,
-                                   c->opt.colour_mode == SG_COLOUR_LEX ? 2 : 1);
+                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2);
             else
                 hipLaunchKernelGGL((k_vcycle_fused<T, false>), dim3(width), dim3(512), (size_t)off * sizeof(T), c->stream, fl,
-                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2,
-                                   c->opt.colour_mode == SG_COLOUR_LEX ? 2 : 1);
+                                   (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2);
         } else {
             Level& lc = c->levels[L];
             hipLaunchKernelGGL(k_coarse<T>, dim3(width), dim3(256), (size_t)lc.N * sizeof(double), c->stream, c->kinv,

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "sg_internal.h"
+#include "sg_wave.h"
 
 namespace sg {
 
@@ -45,22 +46,6 @@ __host__ __device__ inline int strip_count(int nx) {
     return 2 + (nx - (kStrip - kStripHalo) - (kStrip - kStripHalo - 1) + kStripCore - 1) / kStripCore;
 }
 __host__ __device__ inline int strip_begin(int s) { return s == 0 ? 0 : kStripCore * s + kStripHalo; }
-
-// lane i's value of lane i - 1 (0 in lane 0) and of lane i + 1 (0 in lane 63)
-__device__ __forceinline__ float from_left(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float from_right(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double from_left(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double from_right(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true));
-}
 
 // M modes of the lane's two nodes of a row: even column, odd column
 template <typename T, int M>
@@ -293,19 +278,10 @@ struct Stencils {
             load(2 * k + 4);
         }
     }
-    // LDS writes done and every wavefront here (loads stay in flight)
     __device__ __forceinline__ void meet() const {
-        if constexpr (SH) {
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __asm__ __volatile__("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            __asm__ __volatile__("" ::: "memory");
-        }
+        if constexpr (SH) lds_meet();
     }
 };
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 
 // K u at the even / odd column: the share of the row below or above (its coefficients from st.e[R] or
 // st.o[R] on), and of the left and right neighbours (the even node's left one is the odd node of the lane
