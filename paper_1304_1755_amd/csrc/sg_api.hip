@@ -86,7 +86,7 @@ int ensure_mg(sg_ctx* c, int is_float) {
     const int P = c->hs.P;
     for (size_t l = 0; l < c->levels.size(); ++l) {
         Level& lv = c->levels[l];
-        const size_t cap = panel_elems(lv.N, P);
+        const size_t cap = panel_elems(lv.N, P, is_float);
         int rc = SG_OK;
         if (is_float && !lv.r32) {
             rc = dalloc(c, &lv.r32, cap);

@@ -244,7 +244,9 @@ int launch_apply_p1(sg_ctx* c, const Plan& pl, const void* U, int in_float, cons
 // one four-colour cycle level, nu = 1 or 2 sweeps, each leg in one launch (sg_stream.hip); sps: the
 // level's stencils by column pairs, nx odd.  The cycle's own vectors lie in panels of C =
 // stream_modes() modes: panel c holds modes m0 .. m0 + C - 1, m0 = min(C c, width - C), node by node
-// (the last panel repeats modes of the one before when C does not divide the width).  f and the result
+// (the last panel repeats modes of the one before when C does not divide the width; the coarse kernels
+// write a mode's first copy only and the legs then carry the other one's garbage along, which stays in its
+// mode and is not written to a result).  f and the result
 // are node-major with the row strides given, or in panels where the stride is 0.
 // down: uo = nu forward sweeps from zero on f, fc = P^T (f - K uo).  up: uo = nu backward sweeps
 // from ui + P ec; uo must not overlap ui.
@@ -262,8 +264,11 @@ hipError_t stream_up(hipStream_t st, const double* sps, const double* f, int ldf
 inline bool stream_fits(int nx, int ld, size_t size) {
     return (size_t)nx * ld * size * 80 < 0xFFFFFFFFull && (size_t)(nx + 1) * 10 * (nx + 3) * size < 0xFFFFFFFFull;
 }
-// elements of a block of `width` modes on N nodes, in panels or node-major
-inline size_t panel_elems(size_t N, int width) { return N * (width + 3); }
+// elements that hold a block of any width up to `width` on N nodes, in panels or node-major
+inline size_t panel_elems(size_t N, int width, int is_float) {
+    const int M = stream_modes(is_float, width);
+    return N * ((width + M - 1) / M * M);
+}
 // panel c of N nodes and pc modes each: offset of mode `col` of node 0 (nodes pc apart)
 __host__ __device__ inline size_t panel_offset(int col, int width, int pc, size_t N) {
     const int c = col / pc, m0 = c * pc < width - pc ? c * pc : width - pc;

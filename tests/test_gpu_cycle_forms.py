@@ -124,3 +124,21 @@ def test_values_of_the_modes_a_panel_repeats_are_dropped():
                 g.vcycle(torch.full((g.N, w), float("nan"), dtype=dt, device="cuda"), prec=prec)
             assert torch.equal(g.vcycle(f, prec=prec), want)
         g.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_cycle_buffers_of_one_mode(prec):
+    """The first cycle allocates three vectors of the finest level, four of the coarser ones (a third of its nodes
+    together) and one staging vector in double; a few granules of the allocator may come on top."""
+    import paper_1304_1755_amd as sgbt
+    note(f"cycle buffers P=1 {prec}")
+    g = sgbt.Problem(1024, 0, 0, 0.3)
+    f = torch.ones((g.N, 1), dtype=torch.float32 if prec == "f32" else torch.float64, device="cuda")
+    u = torch.empty_like(f)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    g.vcycle(f, u, prec=sgbt.SG_F32 if prec == "f32" else sgbt.SG_F64)
+    torch.cuda.synchronize()
+    held = before - torch.cuda.mem_get_info()[0]
+    assert held <= g.N * (f.element_size() * (3 + 4 / 3) + 8) + 30 * 2 ** 21
+    g.close()
