@@ -269,10 +269,10 @@ inline size_t panel_elems(size_t N, int width, int is_float) {
     const int M = stream_modes(is_float, width);
     return N * ((width + M - 1) / M * M);
 }
-// panel c of N nodes and pc modes each: offset of mode `col` of node 0 (nodes pc apart)
+// offset of mode `col` of node 0 among panels of pc = 1, 2 or 4 modes on N nodes (nodes pc apart)
 __host__ __device__ inline size_t panel_offset(int col, int width, int pc, size_t N) {
-    const int c = col / pc, m0 = c * pc < width - pc ? c * pc : width - pc;
-    return (size_t)c * N * pc + (col - m0);
+    const int m0 = col & -pc, last = width - pc;
+    return (size_t)m0 * N + (col - (m0 < last ? m0 : last));
 }
 int launch_vcycle(sg_ctx* c, const void* f, int ldf, void* u, int ldu, int width, int is_float);
 // a level's device arrays made from its sten64: sten32, rdiag, stp, and where allocated sps (nx odd), cst, lex

@@ -1584,7 +1584,8 @@ __device__ __forceinline__ void coarsest_solve(const double* __restrict__ kinv, 
 template <typename T>
 constexpr int fused4_threads() { return sizeof(T) == 4 ? 1024 : 256; }
 
-template <typename T>
+// PANEL as for k_vcycle_pad
+template <typename T, bool PANEL>
 __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_fused4(FusedLevels<T> fl, const double* __restrict__ kinv,
                                                         const T* __restrict__ fin, int ldf, T* __restrict__ uout,
                                                         int ldu, int nu1, int nu2, int pc) {
@@ -1593,14 +1594,12 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_fused4(FusedLeve
     T* r = lds + fl.roff;
     SG_POISON_LDS(lds, fl.roff + fl.nx[0] * fl.nx[0]);
     const int col = blockIdx.x;
-    // the column's offset: blocks in panels of pc modes (node strides ldf = ldu = pc), or node-major
-    const size_t cin = pc ? panel_offset(col, gridDim.x, pc, fl.nx[0] * fl.nx[0]) : col;
-    const size_t cout = pc ? panel_offset(col, gridDim.x, pc, fl.nx[0] * fl.nx[0]) : col;
+    const size_t c0 = PANEL ? panel_offset(col, gridDim.x, pc, fl.nx[0] * fl.nx[0]) : col;  // the column
     const int L = fl.nlev - 1;
     {
         const int N0 = fl.nx[0] * fl.nx[0];
         T* f0 = lds + fl.off[0] + N0;
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[cin + (size_t)i * ldf];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[c0 + (size_t)i * ldf];
     }
     __syncthreads();
     OwnNodes<T> on;
@@ -1643,7 +1642,7 @@ __global__ void __launch_bounds__(fused4_threads<T>()) k_vcycle_fused4(FusedLeve
     {
         const int N0 = fl.nx[0] * fl.nx[0];
         const T* u0 = lds + fl.off[0];
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) uout[cout + (size_t)i * ldu] = u0[i];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) uout[c0 + (size_t)i * ldu] = u0[i];
     }
 }
 
@@ -1772,7 +1771,9 @@ constexpr int pad_threads() {
     return LEX && (four < kLexThreads) ? kLexThreads : four;
 }
 
-template <typename T, bool LEX>
+// PANEL: f and u in panels of pc modes, node strides ldf = ldu = pc (an argument that tells the two layouts apart
+// costs every cycle 0.2 us)
+template <typename T, bool LEX, bool PANEL>
 __global__ void __launch_bounds__((pad_threads<T, LEX>())) k_vcycle_pad(PadLevels<T> pl, const double* __restrict__ kinv,
                                                                     const T* __restrict__ fin, int ldf,
                                                                     T* __restrict__ uout, int ldu, int nu1, int nu2, int pc) {
@@ -1782,9 +1783,7 @@ __global__ void __launch_bounds__((pad_threads<T, LEX>())) k_vcycle_pad(PadLevel
     T* lds = (T*)smem_raw;
     SG_POISON_LDS(lds, pl.roff + pl.nx[0] * pl.nx[0]);
     const int col = blockIdx.x;
-    // the column's offset: blocks in panels of pc modes (node strides ldf = ldu = pc), or node-major
-    const size_t cin = pc ? panel_offset(col, gridDim.x, pc, pl.nx[0] * pl.nx[0]) : col;
-    const size_t cout = pc ? panel_offset(col, gridDim.x, pc, pl.nx[0] * pl.nx[0]) : col;
+    const size_t c0 = PANEL ? panel_offset(col, gridDim.x, pc, pl.nx[0] * pl.nx[0]) : col;  // the column
     const int L = pl.nlev - 1;
     const int nx0 = pl.nx[0], N0 = nx0 * nx0;
     // zero every padded u: the border stays zero, the interiors are the zero initial guesses
@@ -1795,7 +1794,7 @@ __global__ void __launch_bounds__((pad_threads<T, LEX>())) k_vcycle_pad(PadLevel
     }
     {
         T* f0 = lds + pl.foff[0];
-        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[cin + (size_t)i * ldf];
+        for (int i = threadIdx.x; i < N0; i += blockDim.x) f0[i] = fin[c0 + (size_t)i * ldf];
     }
     __syncthreads();
     T* r = lds + pl.roff;
@@ -1886,7 +1885,7 @@ __global__ void __launch_bounds__((pad_threads<T, LEX>())) k_vcycle_pad(PadLevel
         const T* u0 = lds + pl.uoff[0];
         for (int i = threadIdx.x; i < N0; i += blockDim.x) {
             const int y = i / nx0, x = i - y * nx0;
-            uout[cout + (size_t)i * ldu] = u0[(y + 1) * (nx0 + 2) + x + 1];
+            uout[c0 + (size_t)i * ldu] = u0[(y + 1) * (nx0 + 2) + x + 1];
         }
     }
 }
@@ -2209,11 +2208,12 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
             pl.roff = off;
             off += c->levels[Lc].N;
             if (lex)
-                hipLaunchKernelGGL((k_vcycle_pad<T, true>), dim3(width), dim3((pad_threads<T, true>())), (size_t)off * sizeof(T),
+                hipLaunchKernelGGL((k_vcycle_pad<T, true, false>), dim3(width), dim3((pad_threads<T, true>())), (size_t)off * sizeof(T),
                                    c->stream, pl, (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc),
                                    c->opt.nu1, c->opt.nu2, pc);
             else
-                hipLaunchKernelGGL((k_vcycle_pad<T, false>), dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
+                hipLaunchKernelGGL((pc ? k_vcycle_pad<T, false, true> : k_vcycle_pad<T, false, false>), dim3(width),
+                                   dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, pl, (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc),
                                    c->opt.nu1, c->opt.nu2, pc);
         } else if (Lc >= 0) {
@@ -2237,7 +2237,8 @@ int vcycle_t(sg_ctx* c, const T* f0, int ldf0, T* u0, int ldu0, int width) {
             fl.p1 = p1;
             off += c->levels[Lc].N;
             if (c->opt.colour_mode == SG_COLOUR_FOUR)
-                hipLaunchKernelGGL(k_vcycle_fused4<T>, dim3(width), dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
+                hipLaunchKernelGGL((pc ? k_vcycle_fused4<T, true> : k_vcycle_fused4<T, false>), dim3(width),
+                                   dim3(fused4_threads<T>()), (size_t)off * sizeof(T),
                                    c->stream, fl,
                                    (const double*)c->kinv, fptr(Lc), fld(Lc), uptr(Lc), uld(Lc), c->opt.nu1, c->opt.nu2, pc);
             else if (lex)
