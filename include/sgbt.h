@@ -166,22 +166,23 @@ int sg_residual(sg_ctx* ctx, const double* F, const double* U, double* R);
 /* One batched V-cycle for K_0 (Sec. 4.1, Sec. 6) on `width` right-hand sides:
  * u approximately K_0^{-1} f, zero initial guess.  f, u: device, N x width
  * node-major with row strides ldf, ldu (elements).  prec SG_F64: doubles;
- * SG_F32: floats.  1 <= width <= P. */
+ * SG_F32: floats.  1 <= width <= P.  f and u must not overlap. */
 int sg_vcycle(sg_ctx* ctx, const void* f, int ldf, void* u, int ldu, int width, int prec);
 
 /* Z = B_D^{-1} R with every K_0 solve replaced by one V-cycle (Sec. 4.1).
- * prec SG_F64: R, Z device doubles.  SG_MIXED: R device doubles, Z device floats. */
+ * prec SG_F64: R, Z device doubles.  SG_MIXED: R device doubles, Z device floats.
+ * R and Z must not overlap. */
 int sg_precond_diag(sg_ctx* ctx, const void* R, void* Z, int prec);
 
 /* Z = B_T^{-1} R: forward block Gauss-Seidel sweep over degree levels with
- * one V-cycle per diagonal block (Sec. 4.2).  Precisions as sg_precond_diag. */
+ * one V-cycle per diagonal block (Sec. 4.2).  Precisions and overlap as sg_precond_diag. */
 int sg_precond_tri(sg_ctx* ctx, const void* R, void* Z, int prec);
 
 /* Z = B_S^{-1} R, the block symmetric Gauss-Seidel preconditioner (Sec. 4.2):
  * the forward sweep of sg_precond_tri, then the backward sweep
  * Z_d <- Z_d - V-cycle(sum_k [G_k]_{d,d+1} (x) K_k Z_{d+1}) for d = p-1 .. 0.
  * Symmetric positive definite for double V-cycles (used with PCG).
- * Precisions as sg_precond_diag. */
+ * Precisions and overlap as sg_precond_diag. */
 int sg_precond_sym(sg_ctx* ctx, const void* R, void* Z, int prec);
 
 /* Z = B^{-1} R for the 2 x 2 split of Sec. 4.2, eq. (hierarchical_structure):

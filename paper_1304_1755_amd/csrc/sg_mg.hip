@@ -1143,11 +1143,11 @@ __device__ __forceinline__ void lex_front(int d, int nx, int& ylo, int& yhi) {
 // six against the former sweeps and 63 with two; at 63^2 438, 303 and 268.
 //
 // What bounds it: 3 nx - 2 dependent fronts, about 0.18 us each; the chain itself
-// (a shift and two multiply-adds) would allow a third of that.  A 63^2 sweep of 126
-// columns takes 34 us, 70 with the neighbours read from LDS at every front and the
-// coefficients from a node-ordered array a cache line per lane; the left GMRES solve of
-// the 65 x 65 problem with the 2 x 2 split went from 36.9 to 19.2 ms with this and the
-// coupling of k_split_couple.
+// would allow about a third of that.  A 63^2 sweep of 126 columns takes 34 us (24 from
+// zero), 70 with the neighbours read from LDS at every front and the coefficients from a
+// node-ordered array a cache line per lane; the left GMRES solve of the 65 x 65 problem
+// with the 2 x 2 split went from 37.0 to 18.1 ms with this and the coupling of
+// k_split_couple.
 constexpr int kLexMaxNx = 63;  // at most 64 rows, one per lane
 constexpr int kLexChunk = 7;   // fronts in LDS at a time, one per loading wavefront
 constexpr int kLexAhead = 2;   // chunks on their way

@@ -25,7 +25,8 @@ namespace {
 // Four adjacent lanes per (node, output mode), modes fastest: lane g takes the partners g, g + 4, ... (the
 // K_0 term is lane 3's last), so that a lane's few stencils have all their loads in flight at once; the
 // lanes' sums meet by shuffles.  (With one lane an output the partners' dependent loads run one after
-// another: 17 -> 7 us a launch over 1 to 56 modes on 7^2 to 63^2 nodes.)  The stencils of K_k on this level
+// another: 13.8 -> 5.9 us a launch over the couplings of the 65 x 65 problem's cycles, 1 to 84 modes on 7^2 to
+// 63^2 nodes.)  The stencils of K_k on this level
 // are block k of sten ((m+1) x N x 9); the partners of a mode are packed first in its row of pidx
 // (beta | k << 16), -1 after the last.
 constexpr int kCoupleLanes = 4;

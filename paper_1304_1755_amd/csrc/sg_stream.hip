@@ -10,8 +10,10 @@
 // of sweep 1 updates row 2k+1, phase 2 row 2k, phase 1 of sweep 2 row 2k-1,
 // phase 2 row 2k-2, and the residual follows on rows 2k-3 and 2k-2.  Four rows
 // of values and three of right-hand sides stay in registers; the columns of the
-// adjacent lanes come by DPP wave shifts.  There is no LDS and no barrier, so
-// the wavefronts of a CU hide each other's loads.
+// adjacent lanes come by DPP wave shifts.  The four wavefronts of a workgroup
+// share the strip's stencils through an LDS ring, with one barrier a step; a launch of
+// one or two panels and more than a workgroup per CU has neither, and every
+// wavefront loads its own (stream_shape).
 //
 // Values near the strip's and the segment's ends go stale, as their outer
 // neighbours are missing: by two columns per row phase (F nodes from old S
@@ -22,10 +24,11 @@
 // What bounds it: the vectors cross HBM once per leg (down: f read, u and a
 // quarter-size coarse f written; up: u, f and the coarse u read, u written), 5.5
 // vectors where the row phases take 18.5.  A V(2,2) cycle took 745 us at 511^2,
-// W = 126, float by row phases and takes 448 (1413 and 750 in double; 208 and 118
-// at 255^2, W = 21, double); its legs at 511^2 run at about 2.2 TB/s of those
-// bytes, held back by the latency of two wavefronts a SIMD and by 16-byte pieces of
-// node-major f and u (a cache line each).
+// W = 126, float by row phases and takes 456 (1412 and 753 in double; 207 and 108
+// at 255^2, W = 21, double).  Its legs at 511^2 in float take 134 and 187 us, 2.2 and 2.3 TB/s of
+// those bytes (372 and 571 MB from and to HBM, 1.26 and 1.34 of them), held back by
+// the latency of two wavefronts a SIMD and by 16-byte pieces of node-major f and
+// u (a cache line each).
 #include <type_traits>
 
 #include "sg_internal.h"
@@ -392,8 +395,9 @@ __device__ __forceinline__ void clear(Pair<T, M>& p) {
 // keeps loads from being moved across: hoisted to the start of a step they would not fit in registers
 __device__ __forceinline__ void fence_schedule() { __builtin_amdgcn_sched_barrier(0); }
 
-// wavefronts per SIMD the register budget is set for: with two (256 registers) nothing spills but a few
-// values of the double up leg; three would spill up to 170 (1.50 against 1.16 ms a cycle at W = 126, double)
+// wavefronts per SIMD the register budget is set for: with two (256 registers) nothing spills but up to 32
+// values of the double legs whose wavefronts load their own stencils; three would spill up to 170 (1.50 against
+// 1.16 ms a cycle at W = 126, double)
 template <typename T, int M>
 constexpr int stream_waves() { return M * sizeof(T) == 4 ? 3 : 2; }
 
