@@ -87,19 +87,14 @@ int ensure_mg(sg_ctx* c, int is_float) {
     for (size_t l = 0; l < c->levels.size(); ++l) {
         Level& lv = c->levels[l];
         const size_t cap = panel_elems(lv.N, P, is_float);
-        int rc = SG_OK;
-        if (is_float && !lv.r32) {
-            rc = dalloc(c, &lv.r32, cap);
-            if (!rc) rc = dalloc(c, &lv.w32, cap);
-            if (!rc) rc = dalloc(c, &lv.u32, cap);  // level 0: the cycle's compact iterate
-            if (!rc && l > 0) rc = dalloc(c, &lv.f32, cap);
-        }
-        if (!is_float && !lv.r64) {
-            rc = dalloc(c, &lv.r64, cap);
-            if (!rc) rc = dalloc(c, &lv.w64, cap);
-            if (!rc) rc = dalloc(c, &lv.u64, cap);
-            if (!rc && l > 0) rc = dalloc(c, &lv.f64, cap);
-        }
+        // each buffer on its own: a call that ran out of memory half-way is completed by the next one
+        auto need = [&](auto** v) { return *v ? (int)SG_OK : dalloc(c, v, cap); };
+        int rc;
+        // u of level 0: the cycle's compact iterate
+        if (is_float)
+            (rc = need(&lv.r32)) || (rc = need(&lv.w32)) || (rc = need(&lv.u32)) || (l > 0 && (rc = need(&lv.f32)));
+        else
+            (rc = need(&lv.r64)) || (rc = need(&lv.w64)) || (rc = need(&lv.u64)) || (l > 0 && (rc = need(&lv.f64)));
         if (rc) return rc;
     }
     if (!c->ws.fstage) {
@@ -113,12 +108,11 @@ int ensure_mg(sg_ctx* c, int is_float) {
 }
 
 int ensure_scalars(sg_ctx* c) {
-    if (c->ws.scal) return SG_OK;
-    int rc = dalloc(c, &c->ws.scal, 1024);
-    if (rc) return rc;
-    rc = dalloc(c, &c->ws.partial, (size_t)kRedBlocks * 256);
-    if (rc) return rc;
-    SG_HIP_CHECK(hipHostMalloc((void**)&c->ws.host_scal, 1024 * sizeof(double), hipHostMallocDefault));
+    int rc;
+    if (!c->ws.scal && (rc = dalloc(c, &c->ws.scal, 1024))) return rc;
+    if (!c->ws.partial && (rc = dalloc(c, &c->ws.partial, (size_t)kRedBlocks * 256))) return rc;
+    if (!c->ws.host_scal)
+        SG_HIP_CHECK(hipHostMalloc((void**)&c->ws.host_scal, 1024 * sizeof(double), hipHostMallocDefault));
     return SG_OK;
 }
 

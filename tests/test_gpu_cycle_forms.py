@@ -142,3 +142,27 @@ def test_cycle_buffers_of_one_mode(prec):
     held = before - torch.cuda.mem_get_info()[0]
     assert held <= g.N * (f.element_size() * (3 + 4 / 3) + 8) + 30 * 2 ** 21
     g.close()
+
+
+def test_cycle_after_a_failed_allocation():
+    """With memory for one of the finest level's three buffers the first cycle reports SG_ENOMEM; the next one, with
+    memory again, completes the buffers and gives the usual result."""
+    import paper_1304_1755_amd as sgbt
+    note("cycle after a failed allocation")
+    g = sgbt.Problem(512, 6, 4, 0.3)
+    want = g.vcycle(torch.ones((g.N, 1), dtype=torch.float64, device="cuda")).clone()
+    g.close()
+    g = sgbt.Problem(512, 6, 4, 0.3)
+    f = torch.ones((g.N, 1), dtype=torch.float64, device="cuda")
+    u = torch.zeros_like(f)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    buffer = 8 * g.N * g.P
+    rest = torch.empty((torch.cuda.mem_get_info()[0] - 3 * buffer // 2,), dtype=torch.uint8, device="cuda")
+    with pytest.raises(sgbt.SGError) as e:
+        g.vcycle(f, u)
+    assert e.value.code == sgbt.SG_ENOMEM
+    del rest
+    torch.cuda.empty_cache()
+    assert torch.equal(g.vcycle(f, u), want)
+    g.close()
